@@ -47,7 +47,7 @@ def sgd_flops(n: int, batch: int, k: int, passes: int) -> float:
     return per_pass * passes
 
 
-def kernel_hash(files=("stgd.hip", "stgd_kernel.h")) -> str:
+def kernel_hash(files=("stgd.hip", "stgd_kernel.h", "stgd_args.h")) -> str:
     """Hash of a kernel's sources without comments and blank lines (the
     counters are valid for this code only); by default the STGD kernel's."""
     import re
@@ -949,7 +949,7 @@ def main():
                                 "FP64 sketch/whitener/post"},
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_BF16 / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16, "traffic": counters_traffic(),
-                     "kernel": "sgd_kernel<MmaBF16,128,1,plain>", "flops_per_launch": flops, "launch_ms": sgd_ms,
+                     "kernel": "sgd_kernel<7,one view,plain>", "flops_per_launch": flops, "launch_ms": sgd_ms,
                      "frac_one_cu": achieved / (PEAK_BF16 / 256)},
         "stage_ms": {kname: round(v, 4) for kname, v in stages.items()},
         "sgd_samples_per_s": n * w["passes"] / (sgd_ms * 1e-3),

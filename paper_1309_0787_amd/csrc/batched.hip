@@ -25,7 +25,7 @@
 #include <tuple>
 #include <vector>
 
-#include "stgd_kernel.h"
+#include "stgd_grid.h"
 
 namespace otm {
 namespace {

@@ -1,53 +1,45 @@
-// Entry points of the single-problem STGD (the kernel body is in stgd_kernel.h).
+// Entry points of the single-problem STGD (kernel bodies: stgd_kernel.h, BF16, and
+// stgd_grid.h, FP32 and the smallest BF16 runs).
 #include "stgd_kernel.h"
 
 namespace otm {
 namespace {
 
-template <class M, int KP, int NSTAGE, bool COMP, int NTL, bool OV>
+template <int NT, bool ALIASED, bool COMP>
 __global__ __launch_bounds__(kThreads) void sgd_kernel(SgdArgs g) {
-    __shared__ __attribute__((aligned(16))) SgdSmem<M, KP, NSTAGE, 4> sm;
-    sgd_body<M, KP, NSTAGE, 4, false, COMP, NTL, OV>(g, blockIdx.x, sm);
+    __shared__ __attribute__((aligned(16))) typename SgdMode<NT, ALIASED>::SM sm;
+    sgd_body<NT, ALIASED, COMP>(g, blockIdx.x, sm);
 }
 
-template <class M, int KP, int NSTAGE, bool COMP, bool OV>
-int launch_sgd_v(const SgdArgs& a, int restarts, hipStream_t st) {
-    // BF16 pads k to a multiple of 32: when k + 2 (the components and the two
-    // folded means) fits in one tile less than KP, the last tile row and
-    // column of every k x k product hold only padding and are skipped
-    if constexpr (M::EPL == 8) {
-        if (a.k + 2 <= KP - 16) {
-            hipLaunchKernelGGL((sgd_kernel<M, KP, NSTAGE, COMP, KP / 16 - 1, OV>), dim3(restarts), dim3(kThreads), 0, st, a);
-            return check_launch("sgd_kernel");
-        }
-    }
-    hipLaunchKernelGGL((sgd_kernel<M, KP, NSTAGE, COMP, KP / 16, OV>), dim3(restarts), dim3(kThreads), 0, st, a);
+// Runs without compensation take the variant that keeps no compensation terms.
+template <int NT, bool ALIASED>
+int launch_sgd(const SgdArgs& a, int restarts, hipStream_t st) {
+    if (a.compensated) hipLaunchKernelGGL((sgd_kernel<NT, ALIASED, true>), dim3(restarts), dim3(kThreads), 0, st, a);
+    else hipLaunchKernelGGL((sgd_kernel<NT, ALIASED, false>), dim3(restarts), dim3(kThreads), 0, st, a);
     return check_launch("sgd_kernel");
 }
 
-// Rows read from global memory (no staging) with the three views aliased:
-// the body computes the batch product once (P_B = P_A)
-template <class M, int KP, int NSTAGE, bool COMP>
-int launch_sgd(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    static_assert(smem_bytes<M, KP, NSTAGE>() <= kLdsLimit, "STGD shared memory exceeds 160 KB");
-    if constexpr (NSTAGE == 0) {
-        if (aliased) return launch_sgd_v<M, KP, NSTAGE, COMP, true>(a, restarts, st);
-    }
-    return launch_sgd_v<M, KP, NSTAGE, COMP, false>(a, restarts, st);
+template <int NT>
+int dispatch_views(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
+    return aliased ? launch_sgd<NT, true>(a, restarts, st) : launch_sgd<NT, false>(a, restarts, st);
 }
 
-// Picks the instantiation: the smallest padded k, then the largest batch
-// staging that fits in LDS (one view when the three views alias).  BF16 runs
-// without compensation take the variant that keeps no compensation terms
-// (FP32 keeps them: there they also carry -beta kappa O through the step).
-template <class M, int KP>
-int dispatch_staging(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    constexpr int s1 = staging_for<M, KP>(true), s3 = staging_for<M, KP>(false);
-    if constexpr (M::EPL != 1) {
-        if (!a.compensated)
-            return aliased ? launch_sgd<M, KP, s1, false>(a, restarts, true, st) : launch_sgd<M, KP, s3, false>(a, restarts, false, st);
+// BF16: the instantiation with the fewest tile columns that hold k components.
+// With the components and the two folded means in one tile (k <= 14) a step is one
+// chain of latencies whatever the split, and the grid kernel's is the shorter
+// (k = 10: 0.89 against 1.07 us a step; k = 16: 1.14 against 1.01).
+int dispatch_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
+    if (a.k + 2 <= 16) return launch_sgd_grid_bf16(a, restarts, aliased, st);
+    switch ((a.k + 15) / 16) {
+        case 1: return dispatch_views<1>(a, restarts, aliased, st);
+        case 2: return dispatch_views<2>(a, restarts, aliased, st);
+        case 3: return dispatch_views<3>(a, restarts, aliased, st);
+        case 4: return dispatch_views<4>(a, restarts, aliased, st);
+        case 5: return dispatch_views<5>(a, restarts, aliased, st);
+        case 6: return dispatch_views<6>(a, restarts, aliased, st);
+        case 7: return dispatch_views<7>(a, restarts, aliased, st);
+        default: return dispatch_views<8>(a, restarts, aliased, st);
     }
-    return aliased ? launch_sgd<M, KP, s1, true>(a, restarts, true, st) : launch_sgd<M, KP, s3, true>(a, restarts, false, st);
 }
 
 int run_common(const otm_sgd_params* p, int32_t n, const void* YA, const void* YB, const void* YC,
@@ -65,25 +57,9 @@ int run_common(const otm_sgd_params* p, int32_t n, const void* YA, const void* Y
     a.score = nullptr;
     if (a.start_step == a.end_step && !Phi_comp) return OTM_OK;
     const bool aliased = (YA == YB) && (YB == YC);
-    const int k = p->k;
-    if (p->y_dtype == OTM_F32) {
-        switch ((k + 15) / 16) {
-            case 1: return dispatch_staging<MmaF32, 16>(a, restarts, aliased, st);
-            case 2: return dispatch_staging<MmaF32, 32>(a, restarts, aliased, st);
-            case 3: return dispatch_staging<MmaF32, 48>(a, restarts, aliased, st);
-            case 4: return dispatch_staging<MmaF32, 64>(a, restarts, aliased, st);
-            case 5: return dispatch_staging<MmaF32, 80>(a, restarts, aliased, st);
-            case 6: return dispatch_staging<MmaF32, 96>(a, restarts, aliased, st);
-            case 7: return dispatch_staging<MmaF32, 112>(a, restarts, aliased, st);
-            default: return dispatch_staging<MmaF32, 128>(a, restarts, aliased, st);
-        }
-    }
-    switch ((k + 31) / 32) {
-        case 1: return dispatch_staging<MmaBF16, 32>(a, restarts, aliased, st);
-        case 2: return dispatch_staging<MmaBF16, 64>(a, restarts, aliased, st);
-        case 3: return dispatch_staging<MmaBF16, 96>(a, restarts, aliased, st);
-        default: return dispatch_staging<MmaBF16, 128>(a, restarts, aliased, st);
-    }
+    // FP32 runs and the batched ones (batched.hip) sum in the same order, bit for
+    // bit, so both stay with the grid kernel
+    return p->y_dtype == OTM_F32 ? launch_sgd_grid_f32(a, restarts, aliased, st) : dispatch_bf16(a, restarts, aliased, st);
 }
 
 }  // namespace
