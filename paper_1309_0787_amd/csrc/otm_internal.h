@@ -62,7 +62,7 @@ int gemm_nn_f64(const double* A, int lda, const double* B, int ldb, double* C, i
 size_t cholqr2_ws(int d, int m);
 int cholqr2(const double* Y, int d, int m, double* Q, double* Rinv, int32_t* info, void* ws, hipStream_t s);
 
-// FP64 sparse-dense product (spmm.hip): Y[r, :] = scale sum_j C[r, j] X[j, :]
+// FP64 sparse-dense product (m2.hip): Y[r, :] = scale sum_j C[r, j] X[j, :]
 // for m <= 256 columns, rows of X and Y m apart.  Out-of-range columns are
 // skipped as in every kernel of the library.
 int spmm64(const otm_csr& C, const double* X, int m, double scale, double* Y, hipStream_t s);
@@ -76,6 +76,14 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf16_to_f32(__bf16 x) { return static_cast<float>(x); }
 __device__ __forceinline__ __bf16 f32_to_bf16(float x) { return static_cast<__bf16>(x); }
+
+// Entries [b, e) of a CSR row, clamped to [0, nnz]
+__device__ __forceinline__ void clamp_row(const int32_t* rowptr, int64_t nnz, int row, int64_t& b, int64_t& e) {
+    b = rowptr[row];
+    e = rowptr[row + 1];
+    b = b < 0 ? 0 : (b > nnz ? nnz : b);
+    e = e < b ? b : (e > nnz ? nnz : e);
+}
 
 constexpr int kMaxK = 128;       // STGD capacity (components)
 constexpr int kMaxBatch = 128;   // STGD capacity (mini-batch rows)

@@ -1,0 +1,59 @@
+"""The FP64 second-moment operator at the edges of its dispatch: column counts on
+both sides of the two- and four-columns-per-lane kernels, even and odd, rows of
+C^T short (one wave per row) and long (entries split over waves), with empty
+rows and rows that end inside, at and across the shares of 256 entries; against the dense expression in float64.
+
+Bar: 1e-12 relative (Frobenius): sums of at most 3e4 terms of mixed sign in
+float64 differ by their order in about sqrt(3e4) 2^-53 = 2e-14 of the terms' norm,
+and O takes differences of two such sums up to 10 times their size."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev, rel
+
+from paper_1309_0787_amd import otm
+
+pytestmark = pytest.mark.gpu
+
+
+def _csr(dense):
+    rp = np.concatenate([[0], np.cumsum((dense != 0).sum(1))]).astype(np.int32)
+    r, c = np.nonzero(dense)
+    return rp, c.astype(np.int32), dense[r, c].astype(np.float32)
+
+
+def _dev_csr(rp, ci, v, n_cols):
+    t = [torch.from_numpy(x).to(dev()) for x in (rp, ci, v)]
+    return otm.DeviceCSR(len(rp) - 1, n_cols, t[0], t[1], t[2])
+
+
+@pytest.mark.parametrize("m", [1, 2, 63, 64, 100, 127, 128, 130, 200, 255, 256])
+@pytest.mark.parametrize("n,d,heavy", [(300, 200, False), (2500, 9, False), (2048, 20, True), (700, 1, False)])
+@pytest.mark.parametrize("normalize", [False, True])
+def test_m2_apply(m, n, d, heavy, normalize):
+    g = np.random.default_rng(m * 7 + n + d)
+    C = g.integers(1, 4, (n, d)).astype(np.float64)
+    if d == 200:
+        C *= g.random((n, d)) < 0.1          # short rows of C^T
+        C[:, 5] = 0                          # an empty one
+        C[:, 1:3] += 1
+    elif heavy:
+        C *= g.random((n, d)) < np.linspace(0.05, 1.0, d)   # from 100 entries to 2048
+        C[:, 3] = 0
+        C[:, 0:2] += 1
+    if d == 1:
+        C += 1
+    S = g.standard_normal((d, m))
+    alpha0 = 0.7
+    rs = C.sum(1)
+    a1, a2 = (1 / rs, 1 / (rs * (rs - 1))) if normalize else (np.ones(n), np.ones(n))
+    M1 = C.T @ a1 / n
+    ref = (alpha0 + 1) / n * (C.T @ (a2[:, None] * (C @ S)) - (C.T @ a2)[:, None] * S) - alpha0 * np.outer(M1, M1 @ S)
+    A, AT = _dev_csr(*_csr(C), d), _dev_csr(*_csr(C.T.copy()), n)
+    St = torch.from_numpy(S).to(dev())
+    O = otm.m2_apply(A, AT, normalize, alpha0, St)
+    again = otm.m2_apply(A, AT, normalize, alpha0, St)
+    torch.cuda.synchronize()
+    assert rel(O.cpu().numpy(), ref) < 1e-12
+    assert torch.equal(O, again)             # fixed order of every sum
