@@ -1,7 +1,7 @@
 // FP64 dense linear algebra of the whitening and post-processing steps.
 //
-//  * gemm_tn: C = A^T B for tall A, B (d x p, d x q): split-K partials over row
-//    chunks, then a fixed-order reduction.
+//  * gemm_tn: C = A^T B for tall A, B (d x p, d x q): partial products over row
+//    ranges, then a fixed-order reduction.
 //  * gemm_nn: C = A B with A tall (d x p) and B small (p x q).
 //  * eigenproblems of the small symmetric matrices go to the Jacobi solver of
 //    jacobi.hip.
@@ -21,58 +21,146 @@
 namespace otm {
 namespace {
 
-// ------------------------------------------------------------------ gemm_tn
-constexpr int kTnRows = 16;
+// Both products run on the FP64 matrix instruction (16x16x4: lane l supplies
+// X[l % 16][l / 16] of the first operand, Y[l / 16][l % 16] of the second, and
+// receives rows 4 r + l / 16, r < 4, of column l % 16), operands straight from
+// global memory to registers: a wave's loads for the next step are in flight
+// while the matrix cores work on this one (64 cycles an instruction), and each
+// loaded value serves four to seven instructions, so there is nothing for LDS to
+// add.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
-// A block owns a TILE x TILE tile of C and one chunk of rows; a thread owns
-// the (TILE/16)^2 entries (p0 + ty + 16 i, q0 + tx + 16 j), TILE/32
-// multiply-adds per LDS read (64-tiles for the wide sketch products, 32-tiles
-// where 64 would leave most of a tile empty).  Each entry sums its chunk's
-// rows in order.
-template <int kTnTile>
-__global__ __launch_bounds__(256) void gemm_tn_partial_kernel(const double* __restrict__ A, int lda,
-                                                              const double* __restrict__ B, int ldb, int d, int p,
-                                                              int q, int chunk, double* __restrict__ part) {
-    constexpr int PT = kTnTile / 16;
-    __shared__ double sA[kTnRows][kTnTile + 1];
-    __shared__ double sB[kTnRows][kTnTile + 1];
-    const int p0 = blockIdx.x * kTnTile, q0 = blockIdx.y * kTnTile;
-    const int r0 = blockIdx.z * chunk, r1 = min(d, r0 + chunk);
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    double acc[PT][PT];
+// ------------------------------------------------------------------ gemm_tn
+// C = A^T B: a wave owns up to 4 x 4 tiles of C and a range of rows; A and B are
+// read as they lie (4 rows of 16 consecutive values per load).  The four waves of
+// a workgroup take four ranges of the same tiles and add up through LDS, the
+// workgroups of a tile group leave partial products in `part`.  A Gram matrix
+// (A = B) is symmetric bit for bit: its tile groups below the diagonal are copies.
+// Before and after, us, with the sum of the parts (FMA on 64 x 64 tiles staged in
+// LDS before): d = 50000, Gram of 200 columns 284 -> 76, A^T B of 200 and Gram
+// of 100 columns together 464 -> 168; d = 10000, Gram of 100 columns 67 -> 23;
+// d = 1000, Gram of 20 columns 47 -> 12.  The matrix cores need 58 us for 50000 x
+// 200 x 200 at the 69 TFLOP/s that a large FP64 product reaches, half for a Gram.
+constexpr int kTnT = 4;             // tiles per side of a tile group
+constexpr int kTnMaxParts = 64;
+
+struct TnShape {
+    int tp, tq, gp, gq;             // tiles and tile groups of each side
+    int groups;                     // tile groups computed
+    int nparts, rows;               // workgroups per tile group, rows of each
+};
+
+// About two waves per SIMD over all tile groups, at least 64 rows to a wave
+TnShape tn_shape(int d, int p, int q, bool gram) {
+    TnShape t;
+    t.tp = (p + 15) / 16;
+    t.tq = (q + 15) / 16;
+    t.gp = (t.tp + kTnT - 1) / kTnT;
+    t.gq = (t.tq + kTnT - 1) / kTnT;
+    t.groups = gram ? t.gp * (t.gp + 1) / 2 : t.gp * t.gq;
+    int n = 512 / t.groups;
+    const int most = (d + 255) / 256;
+    n = n < most ? n : most;
+    n = n < kTnMaxParts ? n : kTnMaxParts;
+    t.nparts = n < 1 ? 1 : n;
+    t.rows = ((d + t.nparts - 1) / t.nparts + 15) / 16 * 16;
+    return t;
+}
+
+__global__ __launch_bounds__(256, 2) void gemm_tn_kernel(const double* __restrict__ A, int lda,
+                                                      const double* __restrict__ B, int ldb, int d, int p, int q,
+                                                      TnShape t, bool gram, double* __restrict__ part) {
+    __shared__ f64x4 sacc[kTnT * kTnT][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int gi = 0, gj = blockIdx.x;
+    if (gram) {
+        while (gj >= t.gp - gi) gj -= t.gp - gi++;
+        gj += gi;
+    } else {
+        gi = gj / t.gq;
+        gj -= gi * t.gq;
+    }
+    const int i0 = gi * t.tp / t.gp, ni = (gi + 1) * t.tp / t.gp - i0;
+    const int j0 = gj * t.tq / t.gq, nj = (gj + 1) * t.tq / t.gq - j0;
+    const int per = t.rows / 4;
+    const int r0 = min(d, (int)blockIdx.y * t.rows + w * per), r1 = min(d, r0 + per);
+    f64x4 acc[kTnT][kTnT];
 #pragma unroll
-    for (int i = 0; i < PT; ++i)
+    for (int i = 0; i < kTnT; ++i)
 #pragma unroll
-        for (int j = 0; j < PT; ++j) acc[i][j] = 0.0;
-    for (int rb = r0; rb < r1; rb += kTnRows) {
-        for (int e = threadIdx.x; e < kTnRows * kTnTile; e += 256) {
-            const int rr = e / kTnTile, cc = e % kTnTile;
-            const int r = rb + rr;
-            sA[rr][cc] = (r < r1 && p0 + cc < p) ? A[(size_t)r * lda + p0 + cc] : 0.0;
-            sB[rr][cc] = (r < r1 && q0 + cc < q) ? B[(size_t)r * ldb + q0 + cc] : 0.0;
+        for (int j = 0; j < kTnT; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    // Columns past the matrix read its last one and reach no entry of C; rows past
+    // the range give zeros
+    double a[2][kTnT], b[2][kTnT];
+    const double *pa[kTnT], *pb[kTnT];
+#pragma unroll
+    for (int i = 0; i < kTnT; ++i) {
+        pa[i] = A + min((i0 + min(i, ni - 1)) * 16 + l16, p - 1);
+        pb[i] = B + min((j0 + min(i, nj - 1)) * 16 + l16, q - 1);
+    }
+    auto load = [&](int s, int r) {
+        const int row = r + kq;
+        const size_t oa = (size_t)min(row, d - 1) * lda, ob = (size_t)min(row, d - 1) * ldb;
+#pragma unroll
+        for (int i = 0; i < kTnT; ++i) {
+            a[s][i] = pa[i][oa];
+            b[s][i] = pb[i][ob];
         }
+        if (r + 4 > r1) {
+#pragma unroll
+            for (int i = 0; i < kTnT; ++i) {
+                a[s][i] = row < r1 ? a[s][i] : 0.0;
+                b[s][i] = row < r1 ? b[s][i] : 0.0;
+            }
+        }
+    };
+    auto mul = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < kTnT; ++i)
+#pragma unroll
+            for (int j = 0; j < kTnT; ++j)
+                if (i < ni && j < nj) acc[i][j] = mma64(a[s][i], b[s][j], acc[i][j]);
+    };
+    if (r0 < r1) load(0, r0);
+    for (int r = r0; r < r1; r += 8) {
+        load(1, r + 4);
+        mul(0);
+        load(0, r + 8);
+        mul(1);
+    }
+    for (int u = 1; u < 4; ++u) {
+        if (w == u)
+#pragma unroll
+            for (int i = 0; i < kTnT; ++i)
+#pragma unroll
+                for (int j = 0; j < kTnT; ++j) sacc[i * kTnT + j][lane] = acc[i][j];
         __syncthreads();
-#pragma unroll 4
-        for (int rr = 0; rr < kTnRows; ++rr) {
-            double a[PT], b[PT];
+        if (w == 0)
 #pragma unroll
-            for (int i = 0; i < PT; ++i) a[i] = sA[rr][ty + 16 * i];
+            for (int i = 0; i < kTnT; ++i)
 #pragma unroll
-            for (int j = 0; j < PT; ++j) b[j] = sB[rr][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < PT; ++i)
-#pragma unroll
-                for (int j = 0; j < PT; ++j) acc[i][j] += a[i] * b[j];
-        }
+                for (int j = 0; j < kTnT; ++j) acc[i][j] += sacc[i * kTnT + j][lane];
         __syncthreads();
     }
-    double* out = part + (size_t)blockIdx.z * p * q;
+    if (w != 0) return;
+    double* out = part + (size_t)blockIdx.y * p * q;
 #pragma unroll
-    for (int i = 0; i < PT; ++i)
+    for (int i = 0; i < kTnT; ++i)
 #pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int pi = p0 + ty + 16 * i, qj = q0 + tx + 16 * j;
-            if (pi < p && qj < q) out[(size_t)pi * q + qj] = acc[i][j];
+        for (int j = 0; j < kTnT; ++j) {
+            if (i >= ni || j >= nj) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int pi = (i0 + i) * 16 + 4 * r + kq, qj = (j0 + j) * 16 + l16;
+                if (pi < p && qj < q) {
+                    out[(size_t)pi * q + qj] = acc[i][j][r];
+                    if (gram && gi != gj) out[(size_t)qj * q + pi] = acc[i][j][r];
+                }
+            }
         }
 }
 
@@ -80,87 +168,122 @@ __global__ void reduce_parts_kernel(const double* __restrict__ part, int nparts,
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
     double s = 0.0;
+#pragma unroll 8
     for (int b = 0; b < nparts; ++b) s += part[(size_t)b * m + i];
     out[i] = s;
 }
 
-int tn_chunks(int d) {
-    int c = (d + 511) / 512;
-    return c < 1 ? 1 : (c > 64 ? 64 : c);
+size_t gemm_tn_ws(int d, int p, int q) {
+    return ws_round(sizeof(double) * (size_t)tn_shape(d, p, q, p == q).nparts * p * q);
 }
-
-size_t gemm_tn_ws(int d, int p, int q) { return ws_round(sizeof(double) * (size_t)tn_chunks(d) * p * q); }
 
 int gemm_tn(const double* A, int lda, const double* B, int ldb, int d, int p, int q, double* C, double* part,
             hipStream_t s) {
-    const int nch = tn_chunks(d);
-    const int chunk = (d + nch - 1) / nch;
-    if (p > 128 && q > 128)
-        hipLaunchKernelGGL(gemm_tn_partial_kernel<64>, dim3((p + 63) / 64, (q + 63) / 64, nch), dim3(256), 0, s, A, lda,
-                           B, ldb, d, p, q, chunk, part);
-    else
-        hipLaunchKernelGGL(gemm_tn_partial_kernel<32>, dim3((p + 31) / 32, (q + 31) / 32, nch), dim3(256), 0, s, A, lda,
-                           B, ldb, d, p, q, chunk, part);
-    int st = check_launch("gemm_tn_partial_kernel");
-    if (st != OTM_OK) return st;
+    const bool gram = A == B && lda == ldb && p == q;
+    const TnShape t = tn_shape(d, p, q, gram);
+    double* out = t.nparts > 1 ? part : C;
+    hipLaunchKernelGGL(gemm_tn_kernel, dim3(t.groups, t.nparts), dim3(256), 0, s, A, lda, B, ldb, d, p, q, t, gram, out);
+    int st = check_launch("gemm_tn_kernel");
+    if (st != OTM_OK || t.nparts == 1) return st;
     const int64_t m = (int64_t)p * q;
-    hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, part, nch, m, C);
+    hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, part, t.nparts, m, C);
     return check_launch("reduce_parts_kernel");
 }
 
 // ------------------------------------------------------------------ gemm_nn
-constexpr int kNnM = 64, kNnN = 64, kNnK = 16;
-
+// C = A B: a wave owns MT row tiles and up to NT column tiles of C over the whole
+// contraction.  A is read 16 columns at a time, four consecutive ones per lane
+// (each row's piece is 128 contiguous bytes), so instruction e of a block takes
+// k = k0 + 4 (l / 16) + e from both operands.  MT = 2, NT = 7: B is read once for
+// 32 rows (8 bytes a cycle and CU from L2).  Products with fewer than 1024 such
+// waves take MT = 1, NT = 2: more and shorter chains.  Before and after, us (64 x
+// 64 FMA tiles staged in LDS before): 50000 x 200 x 200 206 -> 107 (the matrix cores
+// need 58), 50000 x 200 x 100 97 -> 49, 10000 x 100 x 100 30 -> 14, 1000 x 20 x 20
+// 7.8 -> 4.6.
+template <int MT, int NT>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__ A, int lda, const double* __restrict__ B,
                                                       int ldb, double* __restrict__ C, int ldc, int d, int p, int q) {
-    __shared__ double sA[kNnK][kNnM + 1];
-    __shared__ double sB[kNnK][kNnN + 1];
-    const int r0 = blockIdx.x * kNnM, c0 = blockIdx.y * kNnN;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;   // rows r0+ty+16i, cols c0+tx+16j
-    double acc[4][4];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r0 = (blockIdx.x * 4 + w) * MT * 16;
+    if (r0 >= d) return;
+    const int tq = (q + 15) / 16;
+    const int j0 = blockIdx.y * tq / gridDim.y, nj = (blockIdx.y + 1) * tq / gridDim.y - j0;
+    f64x4 acc[MT][NT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int k0 = 0; k0 < p; k0 += kNnK) {
-        for (int e = threadIdx.x; e < kNnK * kNnM; e += 256) {
-            const int rr = e / kNnK, kk = e % kNnK;
-            const int r = r0 + rr, kx = k0 + kk;
-            sA[kk][rr] = (r < d && kx < p) ? A[(size_t)r * lda + kx] : 0.0;
+        for (int j = 0; j < NT; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double a[2][MT][4], b[2][NT];
+    // Columns of B past the matrix read its last one and reach no entry of C, nor do
+    // rows of A past it; the contraction's tail gives zeros
+    const double *pa[MT], *pb[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) pa[i] = A + (size_t)min(r0 + i * 16 + l16, d - 1) * lda;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) pb[j] = B + min((j0 + min(j, nj - 1)) * 16 + l16, q - 1);
+    auto load_a = [&](int s, int k0) {
+        if (k0 + 16 <= p) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[s][i][e] = pa[i][k0 + 4 * kq + e];
+        } else {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[s][i][e] = k0 + 4 * kq + e < p ? pa[i][k0 + 4 * kq + e] : 0.0;
         }
-        for (int e = threadIdx.x; e < kNnK * kNnN; e += 256) {
-            const int kk = e / kNnN, cc = e % kNnN;
-            const int kx = k0 + kk, c = c0 + cc;
-            sB[kk][cc] = (kx < p && c < q) ? B[(size_t)kx * ldb + c] : 0.0;
+    };
+    auto load_b = [&](int s, int k0, int e) {
+        const int row = k0 + 4 * kq + e;
+        const size_t ob = (size_t)min(row, p - 1) * ldb;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[s][j] = pb[j][ob];
+        if (k0 + 16 > p) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[s][j] = row < p ? b[s][j] : 0.0;
         }
-        __syncthreads();
+    };
+    load_a(0, 0);
+    load_b(0, 0, 0);
+    auto block = [&](int s, int k0) {
+        load_a(s ^ 1, k0 + 16);
 #pragma unroll
-        for (int kk = 0; kk < kNnK; ++kk) {
-            double a[4], b[4];
+        for (int e = 0; e < 4; ++e) {
+            load_b((e + 1) & 1, e == 3 ? k0 + 16 : k0, (e + 1) & 3);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty + 16 * i];
+            for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = sB[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+                for (int i = 0; i < MT; ++i)
+                    if (j < nj) acc[i][j] = mma64(a[s][i][e], b[e & 1][j], acc[i][j]);
         }
-        __syncthreads();
+    };
+    for (int k0 = 0; k0 < p; k0 += 32) {
+        block(0, k0);
+        if (k0 + 16 < p) block(1, k0 + 16);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + ty + 16 * i, c = c0 + tx + 16 * j;
-            if (r < d && c < q) C[(size_t)r * ldc + c] = acc[i][j];
-        }
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = r0 + i * 16 + 4 * r + kq, c = (j0 + j) * 16 + l16;
+                if (j < nj && row < d && c < q) C[(size_t)row * ldc + c] = acc[i][j][r];
+            }
 }
 
 int gemm_nn(const double* A, int lda, const double* B, int ldb, double* C, int ldc, int d, int p, int q,
             hipStream_t s) {
-    dim3 grid((d + kNnM - 1) / kNnM, (q + kNnN - 1) / kNnN);
-    hipLaunchKernelGGL(gemm_nn_kernel, grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, d, p, q);
+    OTM_REQUIRE(d >= 1 && p >= 1 && q >= 1, OTM_ESHAPE, "gemm_nn needs d, p, q >= 1");
+    const int tq = (q + 15) / 16;
+    if ((int64_t)((d + 31) / 32) * ((tq + 6) / 7) >= 1024)
+        hipLaunchKernelGGL((gemm_nn_kernel<2, 7>), dim3((d + 127) / 128, (tq + 6) / 7), dim3(256), 0, s, A, lda, B, ldb,
+                           C, ldc, d, p, q);
+    else
+        hipLaunchKernelGGL((gemm_nn_kernel<1, 2>), dim3((d + 63) / 64, (tq + 1) / 2), dim3(256), 0, s, A, lda, B, ldb, C,
+                           ldc, d, p, q);
     return check_launch("gemm_nn_kernel");
 }
 
