@@ -400,71 +400,58 @@ __global__ void orth_scale_kernel(const double* __restrict__ V, const double* __
 // pivot is not above 1e-14 of the largest diagonal entry; that pivot is then
 // replaced by the largest diagonal entry so the results stay finite.
 //
-// Blocked by panels of kCholNB columns, three barriers per panel in each
-// half instead of two per column:
-//  * factorization, per panel J = [j0, j1): wave 0 factors the diagonal block
-//    in registers (one lane per packed entry, columns exchanged by
-//    shuffles); every row below solves its kCholNB entries against it; the
-//    trailing rows take the rank-kCholNB update.  The updates of an entry
-//    are applied column by column in the same order as the unblocked
-//    right-looking algorithm.
-//  * inverse X = L^-1 in place, panels from the last: X[i][c] for the rows
-//    below the panel from (X L)[i][c] = 0, i.e.
-//    X[i][c] = -(1/L_cc) sum_{c < l <= i} X[i][l] L[l][c], whose terms with
-//    l past the panel are split over S lanes of a wave; then one thread per
-//    column inverts the diagonal block from (L X)[r][c] = 0.  The new entries
-//    are held in registers (or a small LDS block) until every read of the
-//    panel's L entries is done.  The reciprocals 1/L_jj are kept from the
-//    factorization, so the inverse divides nowhere.
+// Tiles of 16 x 16.  Per tile column: wave 0 factors and inverts the diagonal tile
+// in registers, four columns at a time; the tiles below become A inv^T and the trailing tiles lose
+// L L^T on the matrix cores.  Then X = L^-1: a wave owns a tile column of X and
+// keeps it in registers, X_ij = -inv_ii sum_k L_ik X_kj; the matrix cores return
+// a tile as the second operand of the next product, so L is all that is read
+// from LDS and the columns need no barrier.
+//
+// What bounds it is the chain through the diagonal tiles (m reciprocal square
+// roots and 4 m dependent matrix instructions).  m = 200: 359 -> 119 us, m = 100: 124 -> 42, m =
+// 20: 21 -> 12 (panels of 8 columns on the vector units before, three barriers
+// per panel in each half).
 constexpr int kCholN = 200;
-constexpr int kCholThreads = 1024;
-constexpr int kCholNB = 8;
-constexpr int kCholLoads = 8;      // global loads in flight per thread while filling LDS
+constexpr int kCholT = (kCholN + 15) / 16;
+constexpr int kCholThreads = 512;
+constexpr int kCholWaves = kCholThreads / 64;
+constexpr int kCholLoads = 16;     // global loads in flight per thread while filling LDS
 
 __device__ __forceinline__ int low_idx(int i, int j) { return i * (i + 1) / 2 + j; }
 
-// lane p of the packed nb x nb block: (r, c) with p = r (r + 1) / 2 + c, c <= r
-__device__ __forceinline__ bool block_entry(int p, int nb, int& r, int& c) {
-    r = 0;
-    c = 0;
-    if (p >= nb * (nb + 1) / 2) return false;
-    while ((r + 1) * (r + 2) / 2 <= p) ++r;
-    c = p - r * (r + 1) / 2;
-    return true;
+__device__ __forceinline__ double lane_value(double x, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
 __global__ __launch_bounds__(kCholThreads) void chol_rinv_kernel(const double* __restrict__ G, int m,
                                                                  double* __restrict__ Rinv, int32_t* info, int pass) {
     __shared__ double sL[kCholN * (kCholN + 1) / 2];
-    __shared__ double s_rdiag[kCholN];                 // 1 / L_jj
-    __shared__ double s_xblk[kCholNB * kCholNB];       // inverse of a diagonal block, column-major
     __shared__ double s_dmax;
     __shared__ int s_bad;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    // symmetrized lower triangle 0.5 (G[i][j] + G[j][i]) from coalesced reads
-    // of G in two passes (the lower entries, then the upper ones added); a
-    // thread's loads of a pass are issued together
-    for (int half = 0; half < 2; ++half) {
-        for (int base = 0; base < m * m; base += kCholThreads * kCholLoads) {
-            double g[kCholLoads];
+    // the lower triangle of G (a Gram from gemm_tn: symmetric bit for bit), a
+    // thread's loads issued together
+    for (int base = 0; base < m * m; base += kCholThreads * kCholLoads) {
+        double g[kCholLoads];
 #pragma unroll
-            for (int u = 0; u < kCholLoads; ++u) {
-                const int e = base + u * kCholThreads + tid;
-                g[u] = (e < m * m) ? G[e] : 0.0;
-            }
+        for (int u = 0; u < kCholLoads; ++u) {
+            const int e = base + u * kCholThreads + tid;
+            g[u] = (e < m * m) ? G[e] : 0.0;
+        }
 #pragma unroll
-            for (int u = 0; u < kCholLoads; ++u) {
-                const int e = base + u * kCholThreads + tid;
-                if (e < m * m) {
-                    const int i = e / m, j = e % m;
-                    if (half == 0 && j <= i) sL[low_idx(i, j)] = (j == i) ? g[u] : 0.5 * g[u];
-                    if (half == 1 && j > i) sL[low_idx(j, i)] += 0.5 * g[u];
-                }
+        for (int u = 0; u < kCholLoads; ++u) {
+            const int e = base + u * kCholThreads + tid;
+            if (e < m * m) {
+                const int i = e / m, j = e % m;
+                if (j <= i) sL[low_idx(i, j)] = g[u];
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     if (tid < 64) {
         double dm = 0.0;
         for (int i = lane; i < m; i += 64) dm = fmax(dm, sL[low_idx(i, i)]);
@@ -478,168 +465,178 @@ __global__ __launch_bounds__(kCholThreads) void chol_rinv_kernel(const double* _
     const double dmax = s_dmax;
     const double dfix = dmax > 0.0 ? dmax : 1.0;
 
-    for (int j0 = 0; j0 < m; j0 += kCholNB) {
-        const int nb = min(kCholNB, m - j0), j1 = j0 + nb;
-        // diagonal block, wave 0
-        if (tid < 64) {
-            int r, c;
-            const bool live = block_entry(lane, nb, r, c);
-            double v = live ? sL[low_idx(j0 + r, j0 + c)] : 0.0;
-            bool bad = false;
-            for (int cc = 0; cc < nb; ++cc) {
-                double d = __shfl(v, cc * (cc + 1) / 2 + cc);
-                if (!(d > 1e-14 * dmax)) {   // not positive definite to working precision: reported, pivot replaced
-                    bad = true;
-                    d = dfix;
-                }
-                const double sq = sqrt(d), inv = 1.0 / sq;
-                if (lane == 0) s_rdiag[j0 + cc] = inv;
-                if (live && c == cc) v = (r == cc) ? sq : v * inv;
-                const double lr = __shfl(v, r * (r + 1) / 2 + cc);   // L[r][cc]
-                const double lc = __shfl(v, c * (c + 1) / 2 + cc);   // L[c][cc]
-                if (live && c > cc) v -= lr * lc;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int T = (m + 15) / 16;
+    // First operand (row l16, columns 4 e + kq) of the tile at (r0, c0) below the
+    // diagonal; rows past m read the last one and reach no stored entry
+    auto below = [&](int r0, int c0, double (&x)[4]) {
+        const double* row = sL + low_idx(min(r0 + l16, m - 1), c0 + kq);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = row[4 * e];
+    };
+    // the same of the inverted diagonal tile at r0, which is lower triangular
+    auto diag = [&](int r0, double (&x)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            x[e] = (4 * e + kq <= l16 && r0 + l16 < m) ? sL[low_idx(r0 + l16, r0 + 4 * e + kq)] : 0.0;
+    };
+    for (int P = 0; P < T; ++P) {
+        const int j0 = 16 * P, nb = min(16, m - j0);
+        if (w == 0) {
+            // The tile by symmetry as rows l16, columns 4 r + kq: acc[p] is the
+            // operand that the columns 4 p .. 4 p + 3 make, on either side.  Four
+            // columns at a time: their 4 x 4 block V = L44^-1 on scalars, the
+            // columns of L as V A^T, the rest of the tile less L L^T; then the
+            // inverse, X_p = V_p W_p and W -= L_p X_p from W = I.  Rows past m are
+            // rows of the identity.
+            f64x4 acc, W, V, Lp;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = 4 * r + kq, hi = max(l16, c), lo = min(l16, c);
+                acc[r] = hi < nb ? sL[low_idx(j0 + hi, j0 + lo)] : (hi == lo ? 1.0 : 0.0);
+                W[r] = c == l16 ? 1.0 : 0.0;
             }
-            if (live) sL[low_idx(j0 + r, j0 + c)] = v;
+            bool bad = false;
+            const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                double l[4][4], v[4][4], inv[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int r = c; r < 4; ++r) l[r][c] = lane_value(acc[p], 16 * c + 4 * p + r);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    double d = l[c][c];
+#pragma unroll
+                    for (int k = 0; k < c; ++k) d -= l[c][k] * l[c][k];
+                    if (4 * p + c < nb && !(d > 1e-14 * dmax)) {   // not positive definite to working precision: reported, pivot replaced
+                        bad = true;
+                        d = dfix;
+                    }
+                    inv[c] = rsqrt(d);
+#pragma unroll
+                    for (int r = c + 1; r < 4; ++r) {
+                        double t = l[r][c];
+#pragma unroll
+                        for (int k = 0; k < c; ++k) t -= l[r][k] * l[c][k];
+                        l[r][c] = t * inv[c];
+                    }
+                }
+                double mine = 0.0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = 0; c <= r; ++c) {
+                        double t = 0.0;
+#pragma unroll
+                        for (int k = c; k < r; ++k) t -= l[r][k] * v[k][c];
+                        v[r][c] = (r == c ? 1.0 : t) * inv[r];
+                        if (l16 == r && kq == c) mine = v[r][c];
+                    }
+                V[p] = mine;
+                const double cols = mma64(V[p], acc[p], zero)[0];
+                Lp[p] = l16 >= 4 * p + kq ? cols : 0.0;
+                acc = mma64(-Lp[p], Lp[p], acc);
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const double x = mma64(V[p], W[p], zero)[0];
+                W = mma64(l16 >= 4 * p + 4 ? -Lp[p] : 0.0, x, W);
+                W[p] = x;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 4 * r + kq;
+                if (l16 <= row && row < nb) sL[low_idx(j0 + row, j0 + l16)] = W[r];
+            }
             if (bad && lane == 0) s_bad = 1;
         }
         __syncthreads();
-        // the panel's rows below the block.  Only the last panel can be
-        // narrower than kCholNB, and it has no rows below it, so this phase
-        // and the trailing update always work on full panels.
-        for (int i = j1 + tid; i < m; i += kCholThreads) {
-            double x[kCholNB];
+        if (P + 1 < T) {
+            double v[4];
+            diag(j0, v);
+            for (int i = P + 1 + w; i < T; i += kCholWaves) {
+                double u[4];
+                below(16 * i, j0, u);
+                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int c = 0; c < kCholNB; ++c) x[c] = sL[low_idx(i, j0 + c)];
+                for (int e = 0; e < 4; ++e) acc = mma64(u[e], v[e], acc);
 #pragma unroll
-            for (int c = 0; c < kCholNB; ++c) {
-                double sacc = x[c];
-#pragma unroll
-                for (int t = 0; t < c; ++t) sacc -= x[t] * sL[low_idx(j0 + c, j0 + t)];
-                x[c] = sacc * s_rdiag[j0 + c];
+                for (int r = 0; r < 4; ++r)
+                    if (16 * i + 4 * r + kq < m) sL[low_idx(16 * i + 4 * r + kq, j0 + l16)] = acc[r];
             }
-#pragma unroll
-            for (int c = 0; c < kCholNB; ++c) sL[low_idx(i, j0 + c)] = x[c];
         }
         __syncthreads();
-        // trailing update A[i][l] -= sum_c L[i][c] L[l][c], j1 <= l <= i.  Rows
-        // are taken in pairs (the r-th shortest with the r-th longest), S
-        // threads per pair, so every thread has about the same number of
-        // entries; two entries per iteration, loaded before either is stored.
-        const int w = m - j1;
-        if (w > 0) {
-            const int pairs = (w + 1) / 2;
-            const int S = max(1, kCholThreads / pairs);
-            const int pr = tid / S, sub = tid % S;
-            if (pr < pairs) {
-                const int ia = j1 + pr, ib = m - 1 - pr;   // ia == ib: the middle row of an odd count
-                const int la = ia - j1 + 1, lb = (ib != ia) ? ib - j1 + 1 : 0;
-                double lia[kCholNB], lib[kCholNB];
-#pragma unroll
-                for (int c = 0; c < kCholNB; ++c) {
-                    lia[c] = sL[low_idx(ia, j0 + c)];
-                    lib[c] = sL[low_idx(ib, j0 + c)];
+        int i = P + 1, j = P + 1;                      // this wave's trailing tiles, every kCholWaves-th
+        for (int step = w; ; step = kCholWaves) {
+            for (int x = 0; x < step; ++x)
+                if (++j > i) {
+                    j = P + 1;
+                    ++i;
                 }
-                for (int t = sub; t < la + lb; t += 2 * S) {
-                    const int u = t + S;
-                    const bool two = u < la + lb;
-                    const bool fa = t < la, fb = u < la;
-                    const int l1 = j1 + (fa ? t : t - la), l2 = j1 + (fb ? u : u - la);
-                    double* p1 = sL + low_idx(fa ? ia : ib, l1);
-                    double* p2 = sL + low_idx(fb ? ia : ib, two ? l2 : l1);
-                    const double* L1 = sL + low_idx(l1, j0);
-                    const double* L2 = sL + low_idx(two ? l2 : l1, j0);
-                    double a1 = *p1, a2 = *p2;
-                    double x1[kCholNB], x2[kCholNB];
+            if (i >= T) break;
+            double u[4], v[4];
+            below(16 * i, j0, u);
+            below(16 * j, j0, v);
+            f64x4 acc;
+            const int col = 16 * j + l16;
 #pragma unroll
-                    for (int c = 0; c < kCholNB; ++c) {
-                        x1[c] = L1[c];
-                        x2[c] = L2[c];
-                    }
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * i + 4 * r + kq;
+                acc[r] = (row < m && col <= row) ? sL[low_idx(row, col)] : 0.0;
+            }
 #pragma unroll
-                    for (int c = 0; c < kCholNB; ++c) {
-                        a1 -= (fa ? lia[c] : lib[c]) * x1[c];
-                        a2 -= (fb ? lia[c] : lib[c]) * x2[c];
-                    }
-                    *p1 = a1;
-                    if (two) *p2 = a2;
-                }
+            for (int e = 0; e < 4; ++e) acc = mma64(-u[e], v[e], acc);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * i + 4 * r + kq;
+                if (row < m && col <= row) sL[low_idx(row, col)] = acc[r];
             }
         }
         __syncthreads();
     }
     if (tid == 0 && (pass == 0 || s_bad)) *info = s_bad;
 
-    for (int jb = ((m - 1) / kCholNB) * kCholNB; jb >= 0; jb -= kCholNB) {
-        const int nb = min(kCholNB, m - jb), j1 = jb + nb;
-        const int w = m - j1;
-        // four lanes per row (at most 192 rows): measured faster than wider
-        // splits, whose shuffle reduction costs more than the shorter loop
-        int S = 4;
-        while (S > 1 && S * w > kCholThreads) S >>= 1;
-        const int row = tid / S, sub = tid % S;
-        const bool has_row = w > 0 && row < w;
-        const int i = j1 + row;
-        double xr[kCholNB];
-        if (w > 0) {   // a panel with rows below it is full (nb == kCholNB)
-            double z[kCholNB];
+    // X = L^-1, tile columns w and (the short ones) 2 kCholWaves - 1 - w
+    for (int part = 0; part < 2; ++part) {
+        const int j = part == 0 ? w : 2 * kCholWaves - 1 - w;
+        if (j >= T) continue;
+        f64x4 X[kCholT];
 #pragma unroll
-            for (int c = 0; c < kCholNB; ++c) z[c] = 0.0;
-            if (has_row) {
-                const double* Xi = sL + low_idx(i, 0);
-                for (int l = j1 + sub; l <= i; l += S) {
-                    const double xil = Xi[l];
-                    const double* Ll = sL + low_idx(l, jb);
+        for (int i = 0; i < kCholT; ++i) {
+            if (i >= T) continue;
+            f64x4 t = {0.0, 0.0, 0.0, 0.0};
+            if (i == j) {
 #pragma unroll
-                    for (int c = 0; c < kCholNB; ++c) z[c] += xil * Ll[c];
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 4 * r + kq;
+                    if (l16 <= row && 16 * i + row < m) t[r] = sL[low_idx(16 * i + row, 16 * i + l16)];
                 }
-            }
-            // every lane of a wave takes part (S lanes per row, S a power of two)
+            } else if (i > j) {
+                f64x4 sum = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int c = 0; c < kCholNB; ++c)
-                for (int o = S >> 1; o > 0; o >>= 1) z[c] += __shfl_xor(z[c], o);
+                for (int k = 0; k < i; ++k) {
+                    if (k < j) continue;
+                    double u[4];
+                    below(16 * i, 16 * k, u);
 #pragma unroll
-            for (int c = kCholNB - 1; c >= 0; --c) {
-                double acc = z[c];
-#pragma unroll
-                for (int l = c + 1; l < kCholNB; ++l) acc += xr[l] * sL[low_idx(jb + l, jb + c)];
-                xr[c] = -acc * s_rdiag[jb + c];
-            }
-        }
-        __syncthreads();   // every read of the panel's L entries is done
-        if (has_row && sub == 0) {
-#pragma unroll
-            for (int c = 0; c < kCholNB; ++c) sL[low_idx(i, jb + c)] = xr[c];
-        }
-        // the diagonal block's inverse from L X = I: thread c of wave 0 takes
-        // column c, X[r][c] = -(1/L_rr) sum_{c <= l < r} L[r][l] X[l][c]; the
-        // block is overwritten once every column is done
-        if (tid < nb) {
-            const int c = tid;
-            double xc[kCholNB];
-#pragma unroll
-            for (int r = 0; r < kCholNB; ++r) {
-                xc[r] = 0.0;
-                if (r >= c && r < nb) {
-                    double acc = 0.0;
-#pragma unroll
-                    for (int l = 0; l < r; ++l)
-                        if (l >= c) acc += sL[low_idx(jb + r, jb + l)] * xc[l];
-                    xc[r] = (r == c) ? s_rdiag[jb + r] : -s_rdiag[jb + r] * acc;
+                    for (int e = 0; e < 4; ++e) sum = mma64(u[e], X[k][e], sum);
                 }
-            }
+                double v[4];
+                diag(16 * i, v);
 #pragma unroll
-            for (int r = 0; r < kCholNB; ++r) s_xblk[c * kCholNB + r] = xc[r];
+                for (int e = 0; e < 4; ++e) t = mma64(-v[e], sum[e], t);
+            }
+            X[i] = t;
+            const int col = 16 * j + l16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * i + 4 * r + kq;
+                if (row < m && col < m) Rinv[(size_t)col * m + row] = t[r];
+            }
         }
-        __syncthreads();
-        if (tid < nb * kCholNB) {
-            const int c = tid / kCholNB, r = tid % kCholNB;
-            if (r >= c && r < nb) sL[low_idx(jb + r, jb + c)] = s_xblk[c * kCholNB + r];
-        }
-        __syncthreads();
-    }
-    for (int e = tid; e < m * m; e += kCholThreads) {
-        const int c = e / m, ii = e % m;
-        Rinv[e] = (ii >= c) ? sL[low_idx(ii, c)] : 0.0;
     }
 }
 
