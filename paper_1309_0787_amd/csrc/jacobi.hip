@@ -51,12 +51,15 @@ struct alignas(8) PairSlot {
 __device__ __forceinline__ int roff(int i, int n) { return i * n - (i * (i - 1)) / 2 - i; }
 
 // ------------------------------------------------------------------ LDS form
+// Returns at once where run points to 0 (so does the replay).
 // log_rot[round * npairs + slot], log_pq[round * npairs + slot] = p | q << 16;
 // *rounds = number of rounds performed.
 __global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* __restrict__ Ain, int n,
                                                                  double* __restrict__ evals, int* __restrict__ order,
                                                                  Rot* __restrict__ log_rot, int* __restrict__ log_pq,
-                                                                 int* __restrict__ rounds) {
+                                                                 int* __restrict__ rounds,
+                                                                 const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     __shared__ double sA[kJacLdsN * (kJacLdsN + 1) / 2];
     __shared__ Rot srot[kJacLdsN / 2];
     __shared__ PairSlot spq[kJacLdsN / 2];
@@ -203,7 +206,9 @@ constexpr int kChunkRounds = 32;
 __global__ __launch_bounds__(kApplyThreads) void jacobi_apply_kernel(const Rot* __restrict__ log_rot,
                                                                      const int* __restrict__ log_pq,
                                                                      const int* __restrict__ rounds, int n,
-                                                                     double* __restrict__ V) {
+                                                                     double* __restrict__ V,
+                                                                     const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     __shared__ double sV[kRowsPerWg][kJacLdsN];
     __shared__ Rot sR[kChunkRounds * (kJacLdsN / 2)];
     __shared__ int sPQ[kChunkRounds * (kJacLdsN / 2)];
@@ -359,7 +364,8 @@ size_t log_entries(int n) {
 
 size_t jacobi_ws_bytes(int n) {
     if (n > kJacLdsN) return 0;
-    return ws_round(sizeof(Rot) * log_entries(n)) + ws_round(sizeof(int) * log_entries(n)) + ws_round(sizeof(int));
+    return ws_round(sizeof(Rot) * log_entries(n)) + ws_round(sizeof(int) * log_entries(n)) + 2 * ws_round(sizeof(int)) +
+           (eigen_direct_takes(n) ? eigen_direct_ws(n) : 0);
 }
 
 int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s) {
@@ -369,11 +375,21 @@ int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hip
         Rot* lr = wc.take<Rot>(log_entries(n));
         int* lp = wc.take<int>(log_entries(n));
         int* rounds = wc.take<int>(1);
-        hipLaunchKernelGGL(jacobi_lds_kernel, dim3(1), dim3(kJacThreads), 0, s, A, n, evals, order, lr, lp, rounds);
+        int* redo = nullptr;
+        // From 49 on the direct solver is the faster one (a whitener with kt = 48 or 49
+        // columns, all of it: 656 us by rotations, 364 direct; at kt = 24, k = 12 the
+        // two are even); the rotations run where it says so
+        if (eigen_direct_takes(n)) {
+            redo = wc.take<int>(1);
+            int st = eigen_direct(A, V, n, evals, order, redo, wc.take<char>(eigen_direct_ws(n)), s);
+            if (st != OTM_OK) return st;
+        }
+        hipLaunchKernelGGL(jacobi_lds_kernel, dim3(1), dim3(kJacThreads), 0, s, A, n, evals, order, lr, lp, rounds,
+                           redo);
         int st = check_launch("jacobi_lds_kernel");
         if (st != OTM_OK) return st;
         hipLaunchKernelGGL(jacobi_apply_kernel, dim3((n + kRowsPerWg - 1) / kRowsPerWg), dim3(kApplyThreads), 0, s, lr,
-                           lp, rounds, n, V);
+                           lp, rounds, n, V, redo);
         return check_launch("jacobi_apply_kernel");
     }
     hipLaunchKernelGGL(jacobi_global_kernel, dim3(1), dim3(kJacThreads), 0, s, A, V, n, evals, order);

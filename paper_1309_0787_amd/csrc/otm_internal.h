@@ -49,6 +49,12 @@ int validate_csr_header(const otm_csr* C, const char* name);
 size_t jacobi_ws_bytes(int n);
 int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s);
 
+// The same without rotations (eigen.hip), for the n it takes: V, evals, order as
+// above, A kept; *redo = 1 where they are not to working precision.
+bool eigen_direct_takes(int n);
+size_t eigen_direct_ws(int n);
+int eigen_direct(const double* A, double* V, int n, double* evals, int* order, int* redo, void* ws, hipStream_t s);
+
 // FP64 dense products (dense64.hip): C (p x q) = A^T B for tall A (d x p),
 // B (d x q), split over row chunks into `part` (gemm_tn_f64_ws bytes), then a
 // fixed-order reduction; C (d x q) = A B for tall A (d x p), small B (p x q).
