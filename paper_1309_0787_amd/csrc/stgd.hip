@@ -1,5 +1,5 @@
 // Entry points of the single-problem STGD (kernel bodies: stgd_kernel.h, BF16, and
-// stgd_grid.h, FP32 and the smallest BF16 runs).
+// stgd_grid.h, FP32 and some BF16 runs).
 #include "stgd_kernel.h"
 
 namespace otm {
@@ -24,12 +24,23 @@ int dispatch_views(const SgdArgs& a, int restarts, bool aliased, hipStream_t st)
     return aliased ? launch_sgd<NT, true>(a, restarts, st) : launch_sgd<NT, false>(a, restarts, st);
 }
 
+// BF16 runs that the grid kernel steps through faster, us a step (grid, columns):
+//  * k <= 14, the components and the two folded means in one tile: one chain of
+//    latencies whatever the split (k = 10: 0.89, 1.07);
+//  * 17 <= k <= 30 with batches past 64 rows: two tile columns leave a wave each
+//    with four chunks of the batch (k = 20, 100 rows: 1.20, 1.29; 64 rows: 1.15, 1.07;
+//    k = 16: 1.14, 1.03; k = 32: 1.36, 1.30);
+//  * three views without compensation at 65 <= k <= 96 with batches past 112 rows,
+//    whose staging no wave is left for (k = 72, 128 rows: 4.43, 4.60; 100: 4.43, 4.16).
+bool grid_is_faster(const SgdArgs& a, bool aliased) {
+    if (a.k <= 14) return true;
+    if (a.k >= 17 && a.k <= 30) return a.batch > 64;
+    return a.k >= 65 && a.k <= 96 && !aliased && !a.compensated && a.batch > 112;
+}
+
 // BF16: the instantiation with the fewest tile columns that hold k components.
-// With the components and the two folded means in one tile (k <= 14) a step is one
-// chain of latencies whatever the split, and the grid kernel's is the shorter
-// (k = 10: 0.89 against 1.07 us a step; k = 16: 1.14 against 1.01).
 int dispatch_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    if (a.k + 2 <= 16) return launch_sgd_grid_bf16(a, restarts, aliased, st);
+    if (grid_is_faster(a, aliased)) return launch_sgd_grid_bf16(a, restarts, aliased, st);
     switch ((a.k + 15) / 16) {
         case 1: return dispatch_views<1>(a, restarts, aliased, st);
         case 2: return dispatch_views<2>(a, restarts, aliased, st);

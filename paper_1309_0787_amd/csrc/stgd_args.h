@@ -28,7 +28,8 @@ struct SgdArgs {
     float beta0, inv_tau;
 };
 
-// The grid kernel's single runs (stgd_grid.hip): FP32, and BF16 with k + 2 <= 16.
+// The grid kernel's single runs (stgd_grid.hip): FP32, and BF16 with k <= 30 or, for
+// three views without compensation, 65 <= k <= 96.
 int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);
 

@@ -9,8 +9,8 @@
 //   G  = Phi^T Phi,  O = Phi (G * G)               (matrix cores)
 //   Phi <- Phi + beta (D - kappa O)                 (compensated FP32)
 //
-// (FP32 runs, single and batched, and the smallest BF16 runs; the other BF16 runs
-// are in stgd_kernel.h.)
+// (FP32 runs, single and batched, and some BF16 runs; the other BF16 runs are in
+// stgd_kernel.h.)
 //
 // One workgroup of 8 waves runs one whole online run (all steps), keeping the
 // FP32 master copy of Phi (and its Kahan compensation) in registers.  The

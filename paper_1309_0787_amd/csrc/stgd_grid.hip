@@ -27,6 +27,13 @@ int f32_run(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
                    : launch<MmaF32, KP, s3, true, KP / 16, false>(a, restarts, st);
 }
 
+template <int NTL>
+int bf16_small(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
+    if (a.compensated)
+        return aliased ? launch<MmaBF16, 32, 1, true, NTL, false>(a, restarts, st) : launch<MmaBF16, 32, 3, true, NTL, false>(a, restarts, st);
+    return aliased ? launch<MmaBF16, 32, 1, false, NTL, false>(a, restarts, st) : launch<MmaBF16, 32, 3, false, NTL, false>(a, restarts, st);
+}
+
 }  // namespace
 
 int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
@@ -42,11 +49,13 @@ int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_
     }
 }
 
-// One live tile of the two that a K block holds (k + 2 <= 16)
+// k is padded to whole K blocks of 32; where k + 2 (the components and the two folded
+// means) fits in one tile less, the last tile row and column of every k x k product
+// hold only padding and are skipped
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    if (!a.compensated)
-        return aliased ? launch<MmaBF16, 32, 1, false, 1, false>(a, restarts, st) : launch<MmaBF16, 32, 3, false, 1, false>(a, restarts, st);
-    return aliased ? launch<MmaBF16, 32, 1, true, 1, false>(a, restarts, st) : launch<MmaBF16, 32, 3, true, 1, false>(a, restarts, st);
+    if (a.k > 32) return a.k + 2 <= 80 ? launch<MmaBF16, 96, 3, false, 5, false>(a, restarts, st) : launch<MmaBF16, 96, 3, false, 6, false>(a, restarts, st);
+    if (a.k + 2 <= 16) return bf16_small<1>(a, restarts, aliased, st);
+    return bf16_small<2>(a, restarts, aliased, st);
 }
 
 }  // namespace otm

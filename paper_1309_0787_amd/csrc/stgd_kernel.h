@@ -36,7 +36,7 @@
 // (compensated 4.9 -> 3.9), three views 16.2 -> 5.0 (compensated 16.5 -> 6.3;
 // there the views did not fit beside the exchange buffer and were read from
 // global memory inside the products), k = 128 5.8 -> 4.8, k = 80 3.6 -> 2.9,
-// k = 64 2.3 -> 1.9, k = 48 2.0 -> 1.7, k = 32 1.3 -> 1.2.  Two columns per wave
+// k = 64 2.3 -> 1.8, k = 48 2.0 -> 1.6, k = 32 1.3 -> 1.2.  Two columns per wave
 // pair (5.3) and two per wave at one wave per SIMD (5.2) were slower at k = 100.
 //
 // With NT = ceil(k / 16) < 8 columns the waves left over stage the batch
@@ -217,9 +217,11 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
     // BF16 blocks take two tiles: with an odd number of tiles the last block of O
     // is half empty and takes the 16-row instruction (half the LDS reads)
     constexpr bool kHalfO = NT % 2 == 1;
-    // Small BF16 runs are one chain of latencies: the means' and the update's rows
-    // of ybar stay in registers, and the chunks of a batch run side by side
-    constexpr bool kWide = NT <= 2;
+    // Up to three tile columns (one view: four) a wave has a SIMD to itself and the
+    // registers for it: the chunks of a batch run side by side, and the rows of ybar
+    // stay in registers (k = 40, 128 rows: 1.84 -> 1.60 us a step, k = 64, 100 rows
+    // 2.05 -> 1.84; at k = 64 with three views and past it the registers run out)
+    constexpr bool kWide = NT <= 3 || (NT == 4 && ALIASED);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -456,6 +458,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
         invB = p.nb == B ? invBatch : 1.0f / static_cast<float>(p.nb);
     };
     scalars(p0, g.start_step);
+    if (kSpec && NT <= 4 && act) __builtin_amdgcn_s_setprio(2);   // before the stagers
     f32x4 ybw[kWide ? 2 * NKB * 2 : 1], ycw[kWide ? NT : 1];
     if constexpr (kWide) {
 #pragma unroll
@@ -635,7 +638,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
                     if constexpr (COMP) comp[mt][r] = fmaf(f3, oacc[mt][r], comp[mt][r]);
                     else phi_r[mt][r] = fmaf(-f3, oacc[mt][r], phi_r[mt][r]);
                 }
-            if (w >= 4) __builtin_amdgcn_s_setprio(1);
+            if (NT > 4 && w >= 4) __builtin_amdgcn_s_setprio(1);
             al = g.a * live;
             bmA = g.b * live * mA;
             bmB = g.b * live * mB;
@@ -741,7 +744,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
             if (ch * KB < nb) chunk(ch, IntC<1>{});
         }
 
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (NT > 4) __builtin_amdgcn_s_setprio(0);
         const float bl = beta * live, cb = g.b * invB;
         colsum = add_xor32(add_xor16(colsum));
         const float f1 = bl * invB, cmm = g.c * mA * mB;
