@@ -28,10 +28,6 @@ namespace {
 // while the matrix cores work on this one (64 cycles an instruction), and each
 // loaded value serves four to seven instructions, so there is nothing for LDS to
 // add.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f64x4 mma64(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 
 // ------------------------------------------------------------------ gemm_tn
 // C = A^T B: a wave owns up to 4 x 4 tiles of C and a range of rows; A and B are

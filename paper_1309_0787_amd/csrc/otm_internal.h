@@ -75,6 +75,7 @@ int spmm64(const otm_csr& C, const double* X, int m, double scale, double* Y, hi
 
 // ------------------------------------------------------------- numerics
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -82,6 +83,12 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf16_to_f32(__bf16 x) { return static_cast<float>(x); }
 __device__ __forceinline__ __bf16 f32_to_bf16(float x) { return static_cast<__bf16>(x); }
+
+// One FP64 matrix instruction (16x16x4): lane l supplies X[l % 16][l / 16] and
+// Y[l / 16][l % 16] and receives rows 4 r + l / 16, r < 4, of column l % 16
+__device__ __forceinline__ f64x4 mma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
 // Entries [b, e) of a CSR row, clamped to [0, nnz]
 __device__ __forceinline__ void clamp_row(const int32_t* rowptr, int64_t nnz, int row, int64_t& b, int64_t& e) {

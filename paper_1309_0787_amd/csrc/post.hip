@@ -11,71 +11,107 @@ namespace {
 template <class T>
 __device__ __forceinline__ double ld64(const T* p) { return static_cast<double>(static_cast<float>(*p)); }
 
-// UlT[a*k + i] = u_i[a] / lambda_i with lambda_i = kappa ||phi_i||^3
-__global__ void pi_prep_kernel(const float* __restrict__ Phi, int k, double kappa, double* __restrict__ UlT) {
-    const int i = threadIdx.x;
-    if (i >= k) return;
-    double nn = 0.0;
-    for (int a = 0; a < k; ++a) {
-        const double v = Phi[(size_t)i * k + a];
-        nn += v * v;
+// UlT[a*k + i] = u_i[a] / lambda_i with lambda_i = kappa ||phi_i||^3, one wave per i
+__global__ __launch_bounds__(64) void pi_prep_kernel(const float* __restrict__ Phi, int k, double kappa,
+                                                     double* __restrict__ UlT) {
+    const int i = blockIdx.x, lane = threadIdx.x;
+    double v[(kMaxK + 63) / 64], nn = 0.0;
+#pragma unroll
+    for (int u = 0; u < (kMaxK + 63) / 64; ++u) {
+        v[u] = lane + 64 * u < k ? Phi[(size_t)i * k + lane + 64 * u] : 0.0;
+        nn += v[u] * v[u];
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) nn += __shfl_xor(nn, o);
     const double nrm = sqrt(nn);
     const double lam = kappa * nrm * nn;
-    for (int a = 0; a < k; ++a) UlT[(size_t)a * k + i] = static_cast<double>(Phi[(size_t)i * k + a]) / nrm / lam;
+#pragma unroll
+    for (int u = 0; u < (kMaxK + 63) / 64; ++u)
+        if (lane + 64 * u < k) UlT[(size_t)(lane + 64 * u) * k + i] = v[u] / nrm / lam;
 }
 
-constexpr int kPiSamples = 32;
+// Pi[i][x] from the products of sample x with every u_i / lambda_i: negative parts cut,
+// scaled to sum 1, entries below tau cut, scaled again.  A wave owns 16 samples and
+// all k <= 128 rows on the FP64 matrix cores (four consecutive a per lane and block of
+// 16, as the instruction takes any order of the sum), so a sample's row stays in the
+// registers of four lanes and nothing passes through LDS.  k = 100, n = 50000:
+// 110 -> 67 us (FMA from LDS copies, 32 threads of 256 normalizing, before).
 constexpr int kPiThreads = 256;
+constexpr int kPiSamples = 16 * kPiThreads / 64;
+constexpr int kPiTiles = kMaxK / 16;
 
 template <class TY>
 __global__ __launch_bounds__(kPiThreads) void recover_pi_kernel(const TY* __restrict__ Y, int ldy, int n, int k,
                                                                 const double* __restrict__ UlT, double tau,
                                                                 float* __restrict__ Pi) {
-    __shared__ double sY[kPiSamples][kMaxK + 1];
-    __shared__ double sR[kPiSamples][kMaxK + 1];
-    const int tid = threadIdx.x;
-    const int x0 = blockIdx.x * kPiSamples;
-    for (int e = tid; e < kPiSamples * k; e += kPiThreads) {
-        const int xs = e / k, a = e % k;
-        const int x = x0 + xs;
-        sY[xs][a] = (x < n) ? ld64(Y + (size_t)x * ldy + a) : 0.0;
-    }
-    __syncthreads();
-    const int i = tid % 128, half = tid / 128;   // rows i, samples half*16 .. half*16+15
-    if (i < k) {
-        double acc[16];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x0 = blockIdx.x * kPiSamples + 16 * w, x = x0 + l16;
+    if (x0 >= n) return;
+    const TY* y = Y + (size_t)min(x, n - 1) * ldy;
+    const int nt = (k + 15) / 16;
+    f64x4 acc[kPiTiles];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) acc[u] = 0.0;
-        for (int a = 0; a < k; ++a) {
-            const double w = UlT[(size_t)a * k + i];
+    for (int t = 0; t < kPiTiles; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    // step g: a = 16 (g / 4) + 4 kq + g % 4, its row of UlT loaded a step ahead
+    double v[2][4], f[2][kPiTiles];
+    auto load_y = [&](int b, int a0) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) acc[u] += w * sY[half * 16 + u][a];
+        for (int e = 0; e < 4; ++e) v[b][e] = a0 + 4 * kq + e < k ? ld64(y + a0 + 4 * kq + e) : 0.0;
+    };
+    auto load_u = [&](int b, int a) {
+        const double* u = UlT + (size_t)min(a, k - 1) * k;
+#pragma unroll
+        for (int t = 0; t < kPiTiles; ++t)
+            if (t < nt) f[b][t] = u[min(16 * t + l16, k - 1)];
+    };
+    auto block = [&](int b, int a0) {
+        load_y(b ^ 1, a0 + 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            load_u((e + 1) & 1, e == 3 ? a0 + 16 + 4 * kq : a0 + 4 * kq + e + 1);
+            const bool in = a0 + 4 * kq + e < k;
+#pragma unroll
+            for (int t = 0; t < kPiTiles; ++t)
+                if (t < nt) acc[t] = mma64(in && 16 * t + l16 < k ? f[e & 1][t] : 0.0, v[b][e], acc[t]);
         }
+    };
+    load_y(0, 0);
+    load_u(0, 4 * kq);
+    for (int a0 = 0; a0 < k; a0 += 32) {
+        block(0, a0);
+        if (a0 + 16 < k) block(1, a0 + 16);
+    }
+    double s = 0.0, s2 = 0.0;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) sR[half * 16 + u][i] = acc[u];
-    }
-    __syncthreads();
-    if (tid < kPiSamples) {
-        const int x = x0 + tid;
-        if (x < n) {
-            double s = 0.0;
-            for (int r = 0; r < k; ++r) {
-                const double v = fmax(sR[tid][r], 0.0);
-                sR[tid][r] = v;
-                s += v;
-            }
-            double s2 = 0.0;
-            for (int r = 0; r < k; ++r) {
-                double v = (s > 0.0) ? sR[tid][r] / s : 0.0;
-                if (v < tau) v = 0.0;
-                sR[tid][r] = v;
-                s2 += v;
-            }
-            for (int r = 0; r < k; ++r)
-                Pi[(size_t)r * n + x] = static_cast<float>((s2 > 0.0) ? sR[tid][r] / s2 : 0.0);
+    for (int t = 0; t < kPiTiles; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc[t][r] = fmax(acc[t][r], 0.0);
+            s += acc[t][r];
         }
-    }
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+#pragma unroll
+    for (int t = 0; t < kPiTiles; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (t >= nt) continue;
+            double v = (s > 0.0) ? acc[t][r] / s : 0.0;
+            if (v < tau) v = 0.0;
+            acc[t][r] = v;
+            s2 += v;
+        }
+    s2 += __shfl_xor(s2, 16);
+    s2 += __shfl_xor(s2, 32);
+    if (x >= n) return;
+#pragma unroll
+    for (int t = 0; t < kPiTiles; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * t + 4 * r + kq;
+            if (t < nt && i < k) Pi[(size_t)i * n + x] = static_cast<float>((s2 > 0.0) ? acc[t][r] / s2 : 0.0);
+        }
 }
 
 // ---------------------------------------------------------------- tensor form
@@ -227,7 +263,7 @@ extern "C" int otm_recover_pi(const void* Y, int y_dtype, int32_t ldy, int32_t n
     if (n == 0) return OTM_OK;
     hipStream_t s = as_stream(stream);
     double* UlT = static_cast<double*>(ws);
-    hipLaunchKernelGGL(pi_prep_kernel, dim3(1), dim3(kMaxK), 0, s, Phi, k, 0.5 * (1.0 + theta), UlT);
+    hipLaunchKernelGGL(pi_prep_kernel, dim3(k), dim3(64), 0, s, Phi, k, 0.5 * (1.0 + theta), UlT);
     int st = check_launch("pi_prep_kernel");
     if (st != OTM_OK) return st;
     const dim3 grid((n + kPiSamples - 1) / kPiSamples);

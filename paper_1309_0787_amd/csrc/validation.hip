@@ -5,8 +5,8 @@
 //  * row_stats: mean and centred sum of squares of every row (one workgroup
 //    per row, fixed-order tree reduction).
 //  * pair_stats: for every (i, j), the centred cross sum and the l1 distance
-//    sum over a chunk of the n nodes (16 x 16 output tiles, rows staged in
-//    LDS), then a fixed-order reduction over the chunks.
+//    sum over a range of the n nodes (64 x 64 pairs per workgroup, rows staged
+//    in LDS), then a fixed-order reduction over the ranges.
 //  * finalize: rho, the t statistic T = rho sqrt(n-2)/sqrt(1-rho^2) and the
 //    right p-value P(t_(n-2) > T) through the regularized incomplete beta
 //    function, P(t_nu > T) = I_(nu/(nu+T^2))(nu/2, 1/2) / 2 for T >= 0,
@@ -24,10 +24,11 @@
 namespace otm {
 namespace {
 
-constexpr int kStatThreads = 256;
-constexpr int kTile = 16;
-constexpr int kChunk = 128;          // nodes staged per LDS round
-constexpr int kNodesPerBlock = 2048; // nodes per split of the pair sums
+constexpr int kStatThreads = 1024;
+constexpr int kTile = 64;            // rows of each side per workgroup of pair_stats
+constexpr int kPair = 4;             // pairs per thread and side
+constexpr int kChunk = 64;           // nodes staged per LDS round
+constexpr int kNodesPerBlock = 384;  // nodes per split of the pair sums
 constexpr int kMaxTests = 16384;     // k_hat * k (128 x 128)
 
 __device__ double block_sum(double v, double* red) {
@@ -51,9 +52,11 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __
     const int r = blockIdx.x;
     const float* row = r < kh ? Ph + (size_t)r * n : P + (size_t)(r - kh) * n;
     double s = 0.0;
+#pragma unroll 8
     for (int x = threadIdx.x; x < n; x += kStatThreads) s += row[x];
     const double mu = block_sum(s, red) / n;
     double q = 0.0;
+#pragma unroll 8
     for (int x = threadIdx.x; x < n; x += kStatThreads) {
         const double d = row[x] - mu;
         q += d * d;
@@ -66,41 +69,83 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __
 }
 
 // partials over node split z: cross[z][i][j] = sum_x (a_ix - abar_i)(b_jx - bbar_j),
-// l1[z][i][j] = sum_x |a_ix - b_jx|
-__global__ __launch_bounds__(kTile * kTile) void pair_stats_kernel(const float* __restrict__ Ph, int kh,
-                                                                   const float* __restrict__ P, int k, int n,
-                                                                   const double* __restrict__ mean,
-                                                                   double* __restrict__ cross, double* __restrict__ l1) {
-    __shared__ double sa[kTile][kChunk + 1];
-    __shared__ double sb[kTile][kChunk + 1];
+// l1[z][i][j] = sum_x |a_ix - b_jx|.  A thread owns 4 x 4 pairs, so a node costs it
+// two 16-byte LDS reads and 56 FP64 operations (16 x 16 pairs per workgroup, one
+// per thread, took two reads for 4: k_hat = k = 100, n = 50000 282 -> 185 us; the
+// additions and products alone take 60 at full rate).
+__global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict__ Ph, int kh,
+                                                         const float* __restrict__ P, int k, int n,
+                                                         const double* __restrict__ mean, double* __restrict__ cross,
+                                                         double* __restrict__ l1) {
+    // node-major; the pitch keeps 16-byte reads aligned
+    __shared__ __attribute__((aligned(16))) float sa[kChunk][kTile + 4];
+    __shared__ __attribute__((aligned(16))) float sb[kChunk][kTile + 4];
     const int i0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, z = blockIdx.z;
     const int x0 = z * kNodesPerBlock, x1 = min(n, x0 + kNodesPerBlock);
-    const int ti = threadIdx.x / kTile, tj = threadIdx.x % kTile;
-    double c = 0.0, l = 0.0;
+    const int ti = threadIdx.x / 16 * kPair, tj = threadIdx.x % 16 * kPair;
+    double ma[kPair], mb[kPair], c[kPair][kPair], l[kPair][kPair];
+#pragma unroll
+    for (int u = 0; u < kPair; ++u) {
+        ma[u] = (i0 + ti + u < kh) ? mean[i0 + ti + u] : 0.0;
+        mb[u] = (j0 + tj + u < k) ? mean[kh + j0 + tj + u] : 0.0;
+#pragma unroll
+        for (int v = 0; v < kPair; ++v) c[u][v] = l[u][v] = 0.0;
+    }
+    const bool live = i0 + ti < kh && j0 + tj < k;
+    // the next chunk's rows are loaded while this one is summed
+    constexpr int kLoads = kTile * kChunk / 256;
+    const int cs = threadIdx.x % kChunk, rs = threadIdx.x / kChunk;
+    float pa[kLoads], pb[kLoads];
+    auto load = [&](int xb) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int rr = rs + 256 / kChunk * u, x = xb + cs;
+            pa[u] = (i0 + rr < kh && x < x1) ? Ph[(size_t)(i0 + rr) * n + x] : 0.0f;
+            pb[u] = (j0 + rr < k && x < x1) ? P[(size_t)(j0 + rr) * n + x] : 0.0f;
+        }
+    };
+    load(x0);
     for (int xb = x0; xb < x1; xb += kChunk) {
-        for (int e = threadIdx.x; e < kTile * kChunk; e += kTile * kTile) {
-            const int rr = e / kChunk, cc = e % kChunk;
-            const int x = xb + cc;
-            const int ia = i0 + rr, jb = j0 + rr;
-            sa[rr][cc] = (ia < kh && x < x1) ? (double)Ph[(size_t)ia * n + x] : 0.0;
-            sb[rr][cc] = (jb < k && x < x1) ? (double)P[(size_t)jb * n + x] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            sa[cs][rs + 256 / kChunk * u] = pa[u];
+            sb[cs][rs + 256 / kChunk * u] = pb[u];
         }
         __syncthreads();
-        const int cnt = min(kChunk, x1 - xb);
-        const double ma = (i0 + ti < kh) ? mean[i0 + ti] : 0.0;
-        const double mb = (j0 + tj < k) ? mean[kh + j0 + tj] : 0.0;
+        load(xb + kChunk);
+        const int cnt = live ? min(kChunk, x1 - xb) : 0;
+#pragma unroll 2
         for (int cc = 0; cc < cnt; ++cc) {
-            const double a = sa[ti][cc], b = sb[tj][cc];
-            c += (a - ma) * (b - mb);
-            l += fabs(a - b);
+            const f32x4 af = *reinterpret_cast<const f32x4*>(&sa[cc][ti]);
+            const f32x4 bf = *reinterpret_cast<const f32x4*>(&sb[cc][tj]);
+            double a[kPair], b[kPair], da[kPair], db[kPair];
+#pragma unroll
+            for (int u = 0; u < kPair; ++u) {
+                a[u] = af[u];
+                b[u] = bf[u];
+                da[u] = a[u] - ma[u];
+                db[u] = b[u] - mb[u];
+            }
+#pragma unroll
+            for (int u = 0; u < kPair; ++u)
+#pragma unroll
+                for (int v = 0; v < kPair; ++v) {
+                    c[u][v] += da[u] * db[v];
+                    l[u][v] += fabs(a[u] - b[v]);
+                }
         }
         __syncthreads();
     }
-    const int i = i0 + ti, j = j0 + tj;
-    if (i < kh && j < k) {
-        cross[((size_t)z * kh + i) * k + j] = c;
-        l1[((size_t)z * kh + i) * k + j] = l;
-    }
+#pragma unroll
+    for (int u = 0; u < kPair; ++u)
+#pragma unroll
+        for (int v = 0; v < kPair; ++v) {
+            const int i = i0 + ti + u, j = j0 + tj + v;
+            if (i < kh && j < k) {
+                cross[((size_t)z * kh + i) * k + j] = c[u][v];
+                l1[((size_t)z * kh + i) * k + j] = l[u][v];
+            }
+        }
 }
 
 // log of the regularized incomplete beta's prefactor x^a (1-x)^b / B(a, b),
@@ -154,11 +199,13 @@ __device__ double student_right_tail(double T, double nu) {
 
 __global__ void finalize_kernel(const double* __restrict__ cross, const double* __restrict__ l1p, int nz, int kh, int k,
                                 int n, const double* __restrict__ ss, double* __restrict__ rho,
-                                double* __restrict__ pval, double* __restrict__ l1) {
+                                double* __restrict__ pval, double* __restrict__ l1, int* __restrict__ rank) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= kh * k) return;
     const int i = e / k, j = e % k;
+    rank[e] = 0;   // counted up by rank_kernel
     double c = 0.0, l = 0.0;
+#pragma unroll 8
     for (int z = 0; z < nz; ++z) {
         c += cross[(size_t)z * kh * k + e];
         l += l1p[(size_t)z * kh * k + e];
@@ -177,26 +224,34 @@ __global__ void finalize_kernel(const double* __restrict__ cross, const double* 
     l1[e] = l / n;
 }
 
-// rank of p[e] among the m values (ties: lower position first)
+// rank[e] += values among p[f0 .. f0 + kRankSpan) that come before p[e] (ties: lower
+// position first); whole numbers, so the order of the additions does not matter.
+// One workgroup per span and 256 values: 10000 values 297 -> 25 us (one thread
+// went over all of them for each value).
 constexpr int kRankThreads = 256;
+constexpr int kRankSpan = 256;
 __global__ __launch_bounds__(kRankThreads) void rank_kernel(const double* __restrict__ p, int m, int* __restrict__ rank) {
-    __shared__ double sp[kRankThreads];
+    __shared__ double sp[kRankSpan];
     const int e = blockIdx.x * kRankThreads + threadIdx.x;
+    const int f0 = blockIdx.y * kRankSpan, cnt = min(kRankSpan, m - f0);
     const double pe = e < m ? p[e] : 0.0;
+    for (int t = threadIdx.x; t < cnt; t += kRankThreads) sp[t] = p[f0 + t];
+    __syncthreads();
     int r = 0;
-    for (int b = 0; b < m; b += kRankThreads) {
-        const int f = b + threadIdx.x;
-        sp[threadIdx.x] = f < m ? p[f] : 0.0;
-        __syncthreads();
-        const int cnt = min(kRankThreads, m - b);
+    const int b0 = blockIdx.x * kRankThreads;
+    if (f0 + kRankSpan <= b0) {                        // a span wholly before this block's values
+#pragma unroll 16
+        for (int t = 0; t < kRankSpan; ++t) r += sp[t] <= pe ? 1 : 0;
+    } else if (f0 >= b0 + kRankThreads) {
+#pragma unroll 16
+        for (int t = 0; t < cnt; ++t) r += sp[t] < pe ? 1 : 0;
+    } else {
         for (int t = 0; t < cnt; ++t) {
             const double q = sp[t];
-            const int f2 = b + t;
-            r += (q < pe || (q == pe && f2 < e)) ? 1 : 0;
+            r += (q < pe || (q == pe && f0 + t < e)) ? 1 : 0;
         }
-        __syncthreads();
     }
-    if (e < m) rank[e] = r;
+    if (e < m && r > 0) atomicAdd(&rank[e], r);
 }
 
 // One workgroup: BH adjustment, edges, recovery ratio and error.
@@ -225,16 +280,13 @@ __global__ __launch_bounds__(kBhThreads) void bh_scores_kernel(const double* __r
     }
     bmin[t] = run;
     __syncthreads();
-    if (t == 0) {   // minimum of the later segments, from the last down
-        double acc = INFINITY;
-        for (int u = kBhThreads - 1; u >= 0; --u) {
-            const double v = bmin[u];
-            bmin[u] = acc;
-            acc = fmin(acc, v);
-        }
+    for (int o = 1; o < kBhThreads; o <<= 1) {   // bmin[t]: minimum of segments t and later
+        const double v = t + o < kBhThreads ? bmin[t + o] : INFINITY;
+        __syncthreads();
+        bmin[t] = fmin(bmin[t], v);
+        __syncthreads();
     }
-    __syncthreads();
-    const double later = bmin[t];
+    const double later = t + 1 < kBhThreads ? bmin[t + 1] : INFINITY;
     for (int r = lo; r < hi; ++r) q[r] = fmin(q[r], later);
     __syncthreads();
     for (int e = t; e < m; e += kBhThreads) {
@@ -336,12 +388,13 @@ extern "C" int otm_validate(const float* Pi_hat, int32_t k_hat, const float* Pi,
     hipLaunchKernelGGL(row_stats_kernel, dim3(k_hat + k), dim3(kStatThreads), 0, s, Pi_hat, k_hat, Pi, n, mean, ss);
     if ((st = check_launch("row_stats_kernel")) != OTM_OK) return st;
     dim3 grid((k_hat + kTile - 1) / kTile, (k + kTile - 1) / kTile, nz);
-    hipLaunchKernelGGL(pair_stats_kernel, grid, dim3(kTile * kTile), 0, s, Pi_hat, k_hat, Pi, k, n, mean, cross, l1p);
+    hipLaunchKernelGGL(pair_stats_kernel, grid, dim3(256), 0, s, Pi_hat, k_hat, Pi, k, n, mean, cross, l1p);
     if ((st = check_launch("pair_stats_kernel")) != OTM_OK) return st;
-    hipLaunchKernelGGL(finalize_kernel, dim3((m + 255) / 256), dim3(256), 0, s, cross, l1p, nz, k_hat, k, n, ss, rho,
-                       pval, l1);
+    hipLaunchKernelGGL(finalize_kernel, dim3((m + 63) / 64), dim3(64), 0, s, cross, l1p, nz, k_hat, k, n, ss, rho,
+                       pval, l1, rank);
     if ((st = check_launch("finalize_kernel")) != OTM_OK) return st;
-    hipLaunchKernelGGL(rank_kernel, dim3((m + kRankThreads - 1) / kRankThreads), dim3(kRankThreads), 0, s, pval, m, rank);
+    hipLaunchKernelGGL(rank_kernel, dim3((m + kRankThreads - 1) / kRankThreads, (m + kRankSpan - 1) / kRankSpan),
+                       dim3(kRankThreads), 0, s, pval, m, rank);
     if ((st = check_launch("rank_kernel")) != OTM_OK) return st;
     hipLaunchKernelGGL(bh_scores_kernel, dim3(1), dim3(kBhThreads), 0, s, pval, rank, k_hat, k, threshold, l1, padj,
                        edges, scores);
