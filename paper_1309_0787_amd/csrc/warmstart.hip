@@ -8,11 +8,12 @@
 //            W2 h + b2 (P x P), trained in FP32 and run in BF16 on the
 //            matrix cores;
 //   factors  V0 = Q out[:k, :k] sigma^(1/3).
-// The perceptron's products are one tiled matrix-core GEMM (64 x 64 tiles,
-// four waves of 32 x 32, split over K when the output has few tiles, with a
-// fixed-order reduction that applies bias and ReLU).
+// The perceptron's products are tiled matrix-core GEMMs (128 x 128 tiles in FP32, 64 x
+// 64 for small or unaligned ones and in BF16, split over K when the output has few
+// tiles, with a fixed-order reduction that applies bias and ReLU).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "otm_internal.h"
 
@@ -524,6 +525,128 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T* __restrict__ A, int 
             }
 }
 
+// The same for FP32 operands whose rows are 16-byte aligned: tile 128 x 128 x 16, four
+// waves of 64 x 64, the same products summed in the same order (lane group q supplies
+// k = 4 e + q to instruction e of a K block).  So an operand stored along k goes to
+// LDS with each 4 x 4 of k transposed and is then one 16-byte read per row (rows 20
+// floats apart: every bank once); one stored across k takes four 4-byte reads of rows
+// 144 floats apart.  Global reads are 16 bytes wide, the next block's in flight while
+// this one is multiplied, and LDS holds two blocks (one barrier each).  Batch 256,
+// before (the kernel above: 4-byte loads, waited for before every block) and after,
+// us: forward 402 -> 163 for the two products, backward 328 -> 203 for three (29
+// GFLOP in all, 79 TFLOP/s of the 133 that a large FP32 product reaches here).
+constexpr int WBM = 128, WBK = 16, WPK = WBK + 4, WPM = WBM + 16;
+
+// One operand of the tile: rows x0 .. x0 + 127 of its M (N) side, contiguous along k
+// (T = false) or along that side (T = true), L elements from one row to the next.
+template <bool T>
+struct WideOperand {
+    static constexpr int kFloats = T ? WBK * WPM : WBM * WPK;
+    f32x4 r[2];
+    __device__ void load(const float* __restrict__ X, int L, int x0, int nx, int k0, int ke, int tid) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + 256 * u;
+            const int x = x0 + (T ? 4 * (e & 31) : e >> 2), k = k0 + (T ? e >> 5 : 4 * (e & 3));
+            r[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (x < nx && k < ke) r[u] = *reinterpret_cast<const f32x4*>(X + (T ? (size_t)k * L + x : (size_t)x * L + k));
+        }
+    }
+    __device__ void store(float* __restrict__ lds, int tid) const {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + 256 * u;
+            if constexpr (T) {
+                *reinterpret_cast<f32x4*>(lds + (e >> 5) * WPM + 4 * (e & 31)) = r[u];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) lds[(e >> 2) * WPK + 4 * q + (e & 3)] = r[u][q];
+            }
+        }
+    }
+    // k = 4 e + q, e < 4, of row x
+    __device__ static f32x4 frag(const float* __restrict__ lds, int x, int q) {
+        if constexpr (T) {
+            const float* p = lds + q * WPM + x;
+            return f32x4{p[0], p[4 * WPM], p[8 * WPM], p[12 * WPM]};
+        } else {
+            return *reinterpret_cast<const f32x4*>(lds + x * WPK + 4 * q);
+        }
+    }
+};
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_wide_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B,
+                                                        int ldb, float* __restrict__ C, int ldc, int M, int N, int K,
+                                                        int kc, const float* __restrict__ bias, int relu,
+                                                        float* __restrict__ part) {
+    using OA = WideOperand<TA>;
+    using OB = WideOperand<!TB>;
+    __shared__ __attribute__((aligned(16))) float As[2][OA::kFloats];
+    __shared__ __attribute__((aligned(16))) float Bs[2][OB::kFloats];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+    const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
+    const int l16 = lane & 15, qd = lane >> 4;
+    const int m0 = blockIdx.y * WBM, n0 = blockIdx.x * WBM;
+    const int kb = blockIdx.z * kc, ke = min(K, kb + kc);
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    OA a;
+    OB b;
+    a.load(A, lda, m0, M, kb, ke, tid);
+    b.load(B, ldb, n0, N, kb, ke, tid);
+    a.store(As[0], tid);
+    b.store(Bs[0], tid);
+    __syncthreads();
+    int cur = 0;
+    for (int k0 = kb; k0 < ke; k0 += WBK, cur ^= 1) {
+        const bool more = k0 + WBK < ke;
+        if (more) {
+            a.load(A, lda, m0, M, k0 + WBK, ke, tid);
+            b.load(B, ldb, n0, N, k0 + WBK, ke, tid);
+        }
+        f32x4 fa[4], fb[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            fa[i] = OA::frag(As[cur], wm + i * 16 + l16, qd);
+            fb[i] = OB::frag(Bs[cur], wn + i * 16 + l16, qd);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = MmaT<float>::mma(fa[i][e], fb[j][e], acc[i][j]);
+        if (more) {
+            a.store(As[cur ^ 1], tid);
+            b.store(Bs[cur ^ 1], tid);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = m0 + wm + i * 16 + 4 * qd + r;
+                const int gn = n0 + wn + j * 16 + l16;
+                if (gm >= M || gn >= N) continue;
+                float v = acc[i][j][r];
+                if (part != nullptr) {
+                    part[((size_t)blockIdx.z * M + gm) * N + gn] = v;
+                } else {
+                    if (bias) v += bias[gn];
+                    if (relu) v = fmaxf(v, 0.f);
+                    C[(size_t)gm * ldc + gn] = v;
+                }
+            }
+}
+
 // C = sum_z part[z] (fixed order) + bias, then ReLU, or times the ReLU mask of H
 __global__ void split_reduce_kernel(const float* __restrict__ part, int splits, int M, int N, float* __restrict__ C,
                                     int ldc, const float* __restrict__ bias, int relu, const float* __restrict__ mask,
@@ -532,6 +655,7 @@ __global__ void split_reduce_kernel(const float* __restrict__ part, int splits, 
     if (e >= (size_t)M * N) return;
     const int m = e / N, n = e % N;
     float v = 0.f;
+#pragma unroll 8
     for (int z = 0; z < splits; ++z) v += part[(size_t)z * M * N + e];
     if (bias) v += bias[n];
     if (relu) v = fmaxf(v, 0.f);
@@ -547,7 +671,10 @@ size_t gemm_ws_bytes(int batch) {
     return ws_round(sizeof(float) * (size_t)batch * std::max((size_t)kMaxSplits * kHid, (size_t)4 * kOut));
 }
 
-// picks the split over K so that the grid has at least ~1024 workgroups
+// Picks the split over K so that a grid of 64 x 64 tiles has at least ~1024
+// workgroups, and the kernel: the wide tile takes FP32 products with at least 96 rows
+// and columns (below, most of its 128 would be padding) and 16-byte aligned rows, with
+// the same split, so that the sums are the same.
 template <class T, bool TA, bool TB>
 int gemm(const T* A, int lda, const T* B, int ldb, float* C, int ldc, int M, int N, int K, const float* bias, int relu,
          const float* mask, int ldm, float* ws, size_t ws_bytes, hipStream_t st) {
@@ -556,31 +683,46 @@ int gemm(const T* A, int lda, const T* B, int ldb, float* C, int ldc, int M, int
     while (splits < kMaxSplits && tiles * splits < 1024 && K / (splits * 2) >= 4 * GBK) splits *= 2;
     const int kc = ((K + splits - 1) / splits + GBK - 1) / GBK * GBK;
     splits = (K + kc - 1) / kc;
-    dim3 grid((N + GBN - 1) / GBN, (M + GBM - 1) / GBM, splits);
-    if (splits == 1 && mask == nullptr) {   // a mask is applied by the reduction
-        hipLaunchKernelGGL((gemm_kernel<T, TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc, bias,
-                           relu, static_cast<float*>(nullptr));
-        return check_launch("gemm_kernel");
-    }
-    OTM_REQUIRE(ws != nullptr && ws_bytes >= sizeof(float) * (size_t)splits * M * N, OTM_EWORKSPACE,
+    const bool wide = std::is_same_v<T, float> && M >= 96 && N >= 96 && lda % 4 == 0 && ldb % 4 == 0 &&
+                      (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0 &&
+                      ((TA && !TB) || K % 4 == 0) && (!TA || M % 4 == 0) && (TB || N % 4 == 0);
+    const int bm = wide ? WBM : GBM;
+    dim3 grid((N + bm - 1) / bm, (M + bm - 1) / bm, splits);
+    const bool direct = splits == 1 && mask == nullptr;   // a mask is applied by the reduction
+    OTM_REQUIRE(direct || (ws != nullptr && ws_bytes >= sizeof(float) * (size_t)splits * M * N), OTM_EWORKSPACE,
                 "GEMM workspace too small");
-    hipLaunchKernelGGL((gemm_kernel<T, TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc,
-                       static_cast<const float*>(nullptr), 0, ws);
+    const float* b0 = direct ? bias : nullptr;
+    const int relu0 = direct ? relu : 0;
+    float* part = direct ? nullptr : ws;
+    if constexpr (std::is_same_v<T, float>) {
+        if (wide)
+            hipLaunchKernelGGL((gemm_wide_kernel<TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc, b0,
+                               relu0, part);
+    }
+    if (!wide)
+        hipLaunchKernelGGL((gemm_kernel<T, TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc, b0,
+                           relu0, part);
     int s = check_launch("gemm_kernel");
-    if (s != OTM_OK) return s;
+    if (s != OTM_OK || direct) return s;
     const size_t tot = (size_t)M * N;
     hipLaunchKernelGGL(split_reduce_kernel, dim3((tot + 255) / 256), dim3(256), 0, st, ws, splits, M, N, C, ldc, bias,
                        relu, mask, ldm);
     return check_launch("split_reduce_kernel");
 }
 
-// column sums of a batch x N matrix (fixed order)
-__global__ void colsum_kernel(const float* __restrict__ X, int rows, int N, float* __restrict__ out) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+// column sums of a batch x N matrix (fixed order): 64 columns per workgroup, every
+// fourth row per thread (batch 256: 59 -> 5 us; before, one thread per column)
+__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X, int rows, int N,
+                                                     float* __restrict__ out) {
+    __shared__ float part[4][64];
+    const int c = threadIdx.x & 63, g = threadIdx.x >> 6, n = blockIdx.x * 64 + c;
     float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += X[(size_t)r * N + n];
-    out[n] = s;
+    if (n < N)
+#pragma unroll 8
+        for (int r = g; r < rows; r += 4) s += X[(size_t)r * N + n];
+    part[g][c] = s;
+    __syncthreads();
+    if (g == 0 && n < N) out[n] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
 }
 
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -610,6 +752,7 @@ __global__ void mse_kernel(const int32_t* __restrict__ ks, int count, const floa
     const int inst = blockIdx.x, tid = threadIdx.x;
     const int k = ks[inst];
     double s = 0.0;
+#pragma unroll 4
     for (int e = tid; e < kOut; e += 256) {
         const int i = e / kP, j = e % kP;
         const bool live = i < k && j < k;
@@ -627,11 +770,13 @@ __global__ void mse_kernel(const int32_t* __restrict__ ks, int count, const floa
     if (tid == 0) per[inst] = red[0];
 }
 
-__global__ void sum_loss_kernel(const double* __restrict__ per, int count, double inv_cnt, double* __restrict__ loss) {
-    if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(64) void sum_loss_kernel(const double* __restrict__ per, int count, double inv_cnt,
+                                                      double* __restrict__ loss) {
     double s = 0.0;
-    for (int i = 0; i < count; ++i) s += per[i];
-    *loss = s * inv_cnt;
+    for (int i = threadIdx.x; i < count; i += 64) s += per[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (threadIdx.x == 0) *loss = s * inv_cnt;
 }
 
 // Phi (instance i at Phi + i*P*P, phi_j contiguous, length k) = rows of
@@ -783,7 +928,7 @@ extern "C" int otm_mlp_backward(const float* params, int32_t batch, const float*
     int s = gemm<float, true, false>(dout, kOut, H, kHid, grads + kView.w2, kHid, kOut, kHid, batch, nullptr, 0,
                                      nullptr, 0, part, pb, st);
     if (s != OTM_OK) return s;
-    hipLaunchKernelGGL(colsum_kernel, dim3((kOut + 255) / 256), dim3(256), 0, st, dout, batch, kOut, grads + kView.b2);
+    hipLaunchKernelGGL(colsum_kernel, dim3((kOut + 63) / 64), dim3(256), 0, st, dout, batch, kOut, grads + kView.b2);
     if ((s = check_launch("colsum_kernel")) != OTM_OK) return s;
     // dZ = (dout W2) * (H > 0)
     if ((s = gemm<float, false, false>(dout, kOut, params + kView.w2, kHid, dZ, kHid, batch, kHid, kOut, nullptr, 0, H,
@@ -793,7 +938,7 @@ extern "C" int otm_mlp_backward(const float* params, int32_t batch, const float*
     if ((s = gemm<float, true, false>(dZ, kHid, X, kIn, grads + kView.w1, kIn, kHid, kIn, batch, nullptr, 0, nullptr, 0,
                                       part, pb, st)) != OTM_OK)
         return s;
-    hipLaunchKernelGGL(colsum_kernel, dim3((kHid + 255) / 256), dim3(256), 0, st, dZ, batch, kHid, grads + kView.b1);
+    hipLaunchKernelGGL(colsum_kernel, dim3((kHid + 63) / 64), dim3(256), 0, st, dZ, batch, kHid, grads + kView.b1);
     return check_launch("colsum_kernel");
 }
 
