@@ -325,14 +325,15 @@ __global__ void whiten_scale_kernel(const double* __restrict__ V, const double* 
 }
 
 // per column: (max |W[r][j]|, first row reaching it) over a block of rows
-constexpr int kSignBlocks = 128;
-__global__ void colmax_partial_kernel(const double* __restrict__ W, int d, int k, double* __restrict__ pval,
-                                      int* __restrict__ pidx) {
+constexpr int kSignBlocks = 512;
+__global__ __launch_bounds__(128) void colmax_partial_kernel(const double* __restrict__ W, int d, int k,
+                                                             double* __restrict__ pval, int* __restrict__ pidx) {
     const int per = (d + gridDim.x - 1) / gridDim.x;
-    const int r0 = blockIdx.x * per, r1 = min(d, r0 + per);
+    const int r0 = min(d, (int)blockIdx.x * per), r1 = min(d, r0 + per);
     for (int j = threadIdx.x; j < k; j += blockDim.x) {
         double best = -1.0;
-        int bi = r0;
+        int bi = 0;
+#pragma unroll 8
         for (int r = r0; r < r1; ++r) {
             const double v = fabs(W[(size_t)r * k + j]);
             if (v > best) { best = v; bi = r; }
@@ -341,18 +342,25 @@ __global__ void colmax_partial_kernel(const double* __restrict__ W, int d, int k
         pidx[(size_t)blockIdx.x * k + j] = bi;
     }
 }
-
-__global__ void colsign_kernel(const double* __restrict__ W, const double* __restrict__ pval,
-                               const int* __restrict__ pidx, int nparts, int k, double* __restrict__ sign) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= k) return;
+// one wave per column; ties go to the lowest row
+__global__ __launch_bounds__(64) void colsign_kernel(const double* __restrict__ W, const double* __restrict__ pval,
+                                                     const int* __restrict__ pidx, int nparts, int k,
+                                                     double* __restrict__ sign) {
+    const int j = blockIdx.x;
     double best = -1.0;
     int bi = 0;
-    for (int b = 0; b < nparts; ++b) {
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nparts; b += 64) {
         const double v = pval[(size_t)b * k + j];
         if (v > best) { best = v; bi = pidx[(size_t)b * k + j]; }
     }
-    sign[j] = (W[(size_t)bi * k + j] < 0.0) ? -1.0 : 1.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v = __shfl_xor(best, o);
+        const int i = __shfl_xor(bi, o);
+        if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+    }
+    if (threadIdx.x == 0) sign[j] = (W[(size_t)bi * k + j] < 0.0) ? -1.0 : 1.0;
 }
 
 // W *= sign per column; W_lo (row stride ldw_lo, or ldw_lo = k when absent)
@@ -824,7 +832,7 @@ extern "C" int otm_whitener(const double* O, const double* S, int32_t d, int32_t
     if ((st = gemm_nn(Bm, k, Pw, k, W, k, d, k, k, s)) != OTM_OK) return st;
     hipLaunchKernelGGL(colmax_partial_kernel, dim3(kSignBlocks), dim3(128), 0, s, W, d, k, pval, pidx);
     if ((st = check_launch("colmax_partial_kernel")) != OTM_OK) return st;
-    hipLaunchKernelGGL(colsign_kernel, dim3((k + 127) / 128), dim3(128), 0, s, W, pval, pidx, kSignBlocks, k, sgn);
+    hipLaunchKernelGGL(colsign_kernel, dim3(k), dim3(64), 0, s, W, pval, pidx, kSignBlocks, k, sgn);
     if ((st = check_launch("colsign_kernel")) != OTM_OK) return st;
     const int ld_lo = W_lo ? ldw_lo : k;
     const int64_t total = (int64_t)d * ld_lo;
