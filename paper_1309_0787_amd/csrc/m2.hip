@@ -13,16 +13,16 @@
 // are loaded at once, one per lane, and handed on through scalar registers, so
 // an entry costs the vector memory unit one or two wide loads and nothing else
 // (with the index, the value and both weights loaded for every entry, each as a
-// broadcast, it was five to six).  Measured before and after, us: documents
-// (d = 10000, nnz = 1.9e7, m = 100) first pass 2044 -> 883 (17 TB/s of gathers, S
-// stays in L2), second 4504 -> 2345 (6.6 TB/s, T1 is 80 MB; of that gain the even
-// split of the entries is the larger part); graph (n = d = 50000, nnz = 3.7e6,
-// m = 200), where both matrices come from the Infinity Cache at 7.3 TB/s either
-// way, 783 + 848 + 173 for the column sums of M1^T S and the epilogue -> 806 + 867.
+// broadcast, it was five to six: documents' first pass 2044 -> 883 us, 17 TB/s of
+// gathers, S stays in L2).  Matrices past 16 MB are taken by panels of 16 columns.
+// Whole calls before all of this and now, us: documents (d = 10000, nnz = 1.9e7, m =
+// 100) 6600 -> 2540, graph (n = d = 50000, nnz = 3.7e6, m = 200) 1800 -> 1016.
 //
 // Malformed CSR cannot make these kernels read out of bounds: row ranges are
 // clamped to [0, nnz] and entries with a column outside [0, n_cols) are skipped.
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "otm_internal.h"
 
@@ -110,11 +110,12 @@ __device__ __forceinline__ int m2_wave() {
     return __builtin_amdgcn_readfirstlane((blockIdx.x * kM2Threads + threadIdx.x) >> 6);
 }
 
-// T1[t,:] = w2_t sum_j C[t,j] S[j,:]; w1[t], w2[t] from the row sum when normalize;
+// T1[t,:] = w2_t sum_j C[t,j] S[j,:], rows pitch apart, w2 and w1 after column m where
+// the pitch leaves room; w1[t], w2[t] from the row sum when normalize;
 // vpart[block][:] = this block's part of sum_t w1_t sum_j C[t,j] S[j,:]
 template <bool V2, int NU>
 __global__ __launch_bounds__(kM2Threads) void m2_pass1_kernel(otm_csr C, int normalize, const double* __restrict__ S,
-                                                              int m, double* __restrict__ T1, double* __restrict__ w1,
+                                                              int m, int pitch, double* __restrict__ T1, double* __restrict__ w1,
                                                               double* __restrict__ w2, double* __restrict__ vpart,
                                                               int32_t* info) {
     __shared__ double sv[kM2Waves][64 * NU];
@@ -141,12 +142,16 @@ __global__ __launch_bounds__(kM2Threads) void m2_pass1_kernel(otm_csr C, int nor
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int col = m2_col<V2>(lane, u);
-            if (col < m) T1[(size_t)row * m + col] = a2 * acc[u];
+            if (col < m) T1[(size_t)row * pitch + col] = a2 * acc[u];
             vacc[u] += a1 * acc[u];
         }
         if (lane == 0) {
             w1[row] = a1;
             w2[row] = a2;
+            if (pitch >= m + 2) {
+                T1[(size_t)row * pitch + m] = a2;
+                T1[(size_t)row * pitch + m + 1] = a1;
+            }
         }
     }
 #pragma unroll
@@ -160,13 +165,16 @@ __global__ __launch_bounds__(kM2Threads) void m2_pass1_kernel(otm_csr C, int nor
     }
 }
 
-// out[c] = scale sum_b part[b][c], one workgroup per column, in a fixed order
-__global__ __launch_bounds__(256) void m2_colsum_kernel(const double* __restrict__ part, int nparts, int m, double scale,
-                                                        double* __restrict__ out) {
+// out[c] = scale sum_b part[b][c], one workgroup per column, in a fixed order;
+// panels: part[c / 16][b][c % 16]
+__global__ __launch_bounds__(256) void m2_colsum_kernel(const double* __restrict__ part, int nparts, int m, bool panels,
+                                                        double scale, double* __restrict__ out) {
     __shared__ double sw[4];
     const int c = blockIdx.x;
     double t = 0.0;
-    for (int b = threadIdx.x; b < nparts; b += 256) t += part[(size_t)b * m + c];
+    const double* p = panels ? part + (size_t)(c / 16) * nparts * 16 + c % 16 : part + c;
+    const size_t step = panels ? 16 : m;
+    for (int b = threadIdx.x; b < nparts; b += 256) t += p[b * step];
     t = wave_sum(t);
     if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = t;
     __syncthreads();
@@ -219,7 +227,7 @@ __global__ __launch_bounds__(kM2Threads) void m2_pass2_kernel(otm_csr CT, const 
 // whatever rows they belong to.  A wave ends the rows that lie in its share whole;
 // of a row that began before its share it leaves the sums in part[2 wave], of one
 // that goes on past it in part[2 wave + 1] (m columns, then the sums for u and
-// M1), and m2_join_kernel ends those rows.
+// M1), and m2_join_kernel ends those rows.  (For a T1 that the panels below do not take.)
 template <bool V2, int NU>
 __global__ __launch_bounds__(kM2Threads) void m2_split_kernel(otm_csr CT, const double* __restrict__ T1, int m,
                                                               const double* __restrict__ w1, const double* __restrict__ w2,
@@ -295,6 +303,189 @@ __global__ __launch_bounds__(kM2Threads) void m2_join_kernel(otm_csr CT, int m, 
     }
 }
 
+// ---- Panels.  Where S and T1 are far larger than an XCD's 4 MB of L2, every gather
+// of a row comes from the Infinity Cache.  Taken 16 columns at a time (128 bytes, one
+// cache line, of each row; rows padded to whole lines), what the gathers of a panel
+// touch is rows x 128 bytes, and most of it stays in L2 while an XCD works through
+// the panel: workgroup 8 s + x runs on XCD x and takes the s-th piece of that XCD's
+// share of the panels in order.  A wave takes a row's entries eight at a time, eight
+// lanes each.  n = d = 50000, nnz = 3.7e6, m = 200: first pass 806 -> 469 us and 31 to pad
+// S, second 867 -> 459 and 52 for the epilogue (12.6 TB/s of gathers; documents, d =
+// 10000, nnz = 1.9e7, m = 100, T1 of 80 MB: second 2345 -> 1638).
+constexpr int kPanel = 16;
+constexpr int kXcds = 8;
+constexpr int kPanelRows = 64;                         // rows of a workgroup
+
+// panels of m columns and the two that carry w2 and w1 through the second pass
+__host__ __device__ constexpr int panel_count(int m) { return (m + 2 + kPanel - 1) / kPanel; }
+
+__global__ __launch_bounds__(256) void pad_rows_kernel(const double* __restrict__ S, int64_t total, int m, int pitch,
+                                                       double* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= total) return;
+    const int64_t r = e / pitch;
+    const int c = static_cast<int>(e - r * pitch);
+    out[e] = c < m ? S[r * m + c] : 0.0;
+}
+
+// x summed over the eight groups of eight lanes, in every lane
+__device__ __forceinline__ double sum_groups(double x) {
+    x += __shfl_xor(x, 8);
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// This lane's two columns (at x) of sum over the entries [b, e) of A of value times
+// row of X (pitch apart), a part of it in each group of lanes, and the sum of the
+// values, a part in each lane (of every parts-th 64 entries from the part-th on).
+__device__ __forceinline__ void panel_gather(const otm_csr& A, int64_t b, int64_t e, const double* __restrict__ x,
+                                             int pitch, int group, f64x2& acc, double& vals, int part = 0,
+                                             int parts = 1) {
+    constexpr int U = 4;
+    const int lane = threadIdx.x & 63;
+    for (int64_t base = b + part * 64; base < e; base += parts * 64) {
+        const int cnt = e - base < 64 ? static_cast<int>(e - base) : 64;
+        int32_t mc = -1;
+        float mv = 1.0f;
+        if (lane < cnt) {
+            mc = A.colidx[base + lane];
+            if (A.vals) mv = A.vals[base + lane];
+            if (mc < 0 || mc >= A.n_cols) mc = -1;
+        }
+        if (mc >= 0) vals += mv;
+        for (int j = 0; j < cnt; j += 8 * U) {
+            int32_t c[U];
+            f64x2 t[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                c[u] = __shfl(mc, j + 8 * u + group);
+                t[u] = *reinterpret_cast<const f64x2*>(x + (size_t)(c[u] < 0 ? 0 : c[u]) * pitch);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double w = A.vals ? static_cast<double>(__shfl(mv, j + 8 * u + group)) : 1.0;
+                if (c[u] >= 0) acc += w * t[u];
+            }
+        }
+    }
+}
+
+// The panel and the first row of this workgroup's piece; false past this XCD's share
+__device__ __forceinline__ bool panel_piece(int rows, int per, int m, int& panel, int& row0, int& piece) {
+    const int nb = (rows + per - 1) / per;
+    const int64_t total = (int64_t)nb * panel_count(m);
+    const int xcd = blockIdx.x % kXcds;
+    const int64_t g = total * xcd / kXcds + blockIdx.x / kXcds;
+    if (g >= total * (xcd + 1) / kXcds) return false;
+    panel = static_cast<int>(g / nb);
+    row0 = static_cast<int>(g - (int64_t)panel * nb) * per;
+    piece = static_cast<int>(g);
+    return true;
+}
+
+// m2_pass1_kernel by panels: T1 padded to whole panels, w2 and w1 in its columns m and
+// m + 1; vpart[piece][16]
+__global__ __launch_bounds__(kM2Threads) void m2_panel1_kernel(otm_csr C, int normalize, const double* __restrict__ S,
+                                                               int m, double* __restrict__ T1,
+                                                               double* __restrict__ vpart, int32_t* info) {
+    __shared__ f64x2 sv[kM2Waves][8];
+    int panel, row0, piece;
+    if (!panel_piece(C.n_rows, kPanelRows, m, panel, row0, piece)) return;
+    const int lane = threadIdx.x & 63, group = lane >> 3, pitch = panel_count(m) * kPanel;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = panel * kPanel + 2 * (lane & 7);
+    f64x2 vacc = {0.0, 0.0};
+    const int last = min(C.n_rows, row0 + kPanelRows);
+    for (int row = row0 + w; row < last; row += kM2Waves) {
+        int64_t b, e;
+        clamp_row(C.rowptr, C.nnz, row, b, e);
+        f64x2 acc = {0.0, 0.0};
+        double rs = 0.0;
+        panel_gather(C, b, e, S + col, pitch, group, acc, rs);
+        acc[0] = sum_groups(acc[0]);
+        acc[1] = sum_groups(acc[1]);
+        double a1 = 1.0, a2 = 1.0;
+        if (normalize) {
+            rs = wave_sum(rs);
+            if (rs < 2.0) {
+                if (lane == 0) *info = 1;
+                a1 = 0.0;
+                a2 = 0.0;
+            } else {
+                a1 = 1.0 / rs;
+                a2 = 1.0 / (rs * (rs - 1.0));
+            }
+        }
+        vacc += a1 * acc;
+        if (group == 0) {
+            f64x2 t = a2 * acc;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (col + u == m) t[u] = a2;
+                if (col + u == m + 1) t[u] = a1;
+            }
+            *reinterpret_cast<f64x2*>(T1 + (size_t)row * pitch + col) = t;
+        }
+    }
+    if (group == 0) sv[w][lane] = vacc;
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        f64x2 t = sv[0][lane];
+#pragma unroll
+        for (int u = 1; u < kM2Waves; ++u) t += sv[u][lane];
+        *reinterpret_cast<f64x2*>(vpart + (size_t)piece * kPanel + 2 * lane) = t;
+    }
+}
+
+// the sums of the second pass by panels: O = C^T T1, u and M1 from its columns m, m + 1;
+// a wave per row, or (LONG) the four waves of a workgroup on each of its rows
+template <bool LONG>
+__global__ __launch_bounds__(kM2Threads) void m2_panel2_kernel(otm_csr CT, const double* __restrict__ T1, int m,
+                                                               double inv_n, double* __restrict__ O,
+                                                               double* __restrict__ u, double* __restrict__ M1) {
+    constexpr int kRows = LONG ? 1 : kPanelRows;
+    __shared__ f64x2 sv[kM2Waves][8];
+    int panel, row0, piece;
+    if (!panel_piece(CT.n_rows, kRows, m, panel, row0, piece)) return;
+    const int lane = threadIdx.x & 63, group = lane >> 3, pitch = panel_count(m) * kPanel;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = panel * kPanel + 2 * (lane & 7);
+    const int last = min(CT.n_rows, row0 + kRows);
+    for (int row = row0 + (LONG ? 0 : w); row < last; row += kM2Waves) {
+        int64_t b, e;
+        clamp_row(CT.rowptr, CT.nnz, row, b, e);
+        f64x2 acc = {0.0, 0.0};
+        double vals = 0.0;
+        panel_gather(CT, b, e, T1 + col, pitch, group, acc, vals, LONG ? w : 0, LONG ? kM2Waves : 1);
+        acc[0] = sum_groups(acc[0]);
+        acc[1] = sum_groups(acc[1]);
+        if constexpr (LONG) {
+            if (group == 0) sv[w][lane] = acc;
+            __syncthreads();
+            if (threadIdx.x >= 8) return;
+            acc = (sv[0][lane] + sv[1][lane]) + (sv[2][lane] + sv[3][lane]);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (group != 0) continue;
+            if (col + q < m) O[(size_t)row * m + col + q] = acc[q];
+            else if (col + q == m) u[row] = acc[q];
+            else if (col + q == m + 1) M1[row] = acc[q] * inv_n;
+        }
+    }
+}
+
+// O = scale (O - u * S) - alpha0 M1 v^T
+__global__ __launch_bounds__(256) void m2_epilogue_kernel(double* __restrict__ O, const double* __restrict__ S,
+                                                          const double* __restrict__ u, const double* __restrict__ M1,
+                                                          const double* __restrict__ v, int d, int m, double scale,
+                                                          double alpha0) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)d * m) return;
+    const int a = static_cast<int>(idx / m), c = static_cast<int>(idx % m);
+    O[idx] = scale * (O[idx] - u[a] * S[idx]) - alpha0 * M1[a] * v[c];
+}
+
 // Y[row, :] = scale sum_j C[row, j] X[j, :]
 template <bool V2, int NU>
 __global__ __launch_bounds__(kM2Threads) void spmm64_kernel(otm_csr C, const double* __restrict__ X, int m,
@@ -331,6 +522,18 @@ void m2_dispatch(int m, bool aligned, F&& f) {
 int m2_blocks(int64_t waves) {
     const int64_t b = (waves + kM2Waves - 1) / kM2Waves;
     return static_cast<int>(b < 1 ? 1 : (b > kM2MaxBlocks ? kM2MaxBlocks : b));
+}
+
+// Panels pay where a gathered matrix of m doubles a row is well past an XCD's L2, from
+// 16 MB on (whole call without and with them, us: graph 50000 x 50000, nnz = 3.7e6,
+// m = 200 1649, 1016; m = 40 338, 306; 20000 x 20000, nnz = 1.2e6, m = 100 231, 185, m = 64
+// 131, 137; 10000 x 10000, m = 120 99, 114; documents, d = 10000, nnz = 6e6, n = 40000,
+// m = 100 967, 628), and where a panel of 16 columns is not mostly padding.
+bool panels_fit(int rows, int m) { return m >= 32 && (int64_t)rows * m >= 2000000; }
+
+unsigned panel_blocks(int rows, int per, int m) {
+    const int64_t total = (int64_t)((rows + per - 1) / per) * panel_count(m);
+    return static_cast<unsigned>(kXcds * ((total + kXcds - 1) / kXcds));
 }
 
 // Shares of m2_split_kernel at most: enough to fill the device eight times over
@@ -490,6 +693,14 @@ extern "C" size_t otm_m2_apply_workspace(int32_t n, int32_t d, int32_t k_tilde) 
     b += ws_round(sizeof(double) * (size_t)kM2MaxBlocks * k_tilde);
     b += ws_round(sizeof(double) * (size_t)k_tilde);      // v
     b += ws_round(sizeof(double) * (size_t)2 * m2_shares(d) * (k_tilde + 2));
+    if (panels_fit(n, k_tilde)) {                         // padded T1 and S, w1, w2, u, M1, v and its parts
+        const size_t pitch = (size_t)panel_count(k_tilde) * kPanel;
+        size_t p = ws_round(sizeof(double) * pitch * n) + ws_round(sizeof(double) * pitch * d);
+        p += 2 * ws_round(sizeof(double) * (size_t)n) + 2 * ws_round(sizeof(double) * (size_t)d);
+        p += ws_round(sizeof(double) * (size_t)k_tilde);
+        p += ws_round(sizeof(double) * pitch * std::max((size_t)n / kPanelRows + 1, (size_t)kM2MaxBlocks));
+        b = b > p ? b : p;
+    }
     return b;
 }
 
@@ -510,6 +721,51 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
                 "m2_apply workspace too small");
     hipStream_t s = as_stream(stream);
     WsCarver wc(ws, ws_bytes);
+    if (panels_fit(n, k_tilde)) {
+        const int pitch = panel_count(k_tilde) * kPanel;
+        double* T1 = wc.take<double>((size_t)pitch * n);
+        double* Sp = wc.take<double>((size_t)pitch * d);
+        double* w1 = wc.take<double>(n);
+        double* w2 = wc.take<double>(n);
+        double* u = wc.take<double>(d);
+        double* M1 = wc.take<double>(d);
+        double* v = wc.take<double>(k_tilde);
+        int nb = (n + kPanelRows - 1) / kPanelRows;
+        double* vpart = wc.take<double>((size_t)pitch * std::max(nb, kM2MaxBlocks));
+        hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, s, info, 0);
+        if ((st = check_launch("set_i32_kernel")) != OTM_OK) return st;
+        const bool both = panels_fit(d, k_tilde);
+        const int64_t padded = (int64_t)pitch * d, total = (int64_t)d * k_tilde;
+        if (both) {
+            hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, s, S, padded,
+                               k_tilde, pitch, Sp);
+            if ((st = check_launch("pad_rows_kernel")) != OTM_OK) return st;
+            hipLaunchKernelGGL(m2_panel1_kernel, dim3(panel_blocks(n, kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *C,
+                               normalize, Sp, k_tilde, T1, vpart, info);
+        } else {
+            nb = m2_blocks(n);
+            m2_dispatch(k_tilde, reinterpret_cast<uintptr_t>(S) % 16 == 0, [&](auto v2c, auto nuc) {
+                hipLaunchKernelGGL((m2_pass1_kernel<v2c.value, nuc.value>), dim3(nb), dim3(kM2Threads), 0, s, *C,
+                                   normalize, S, k_tilde, pitch, T1, w1, w2, vpart, info);
+            });
+        }
+        if ((st = check_launch("m2 first pass")) != OTM_OK) return st;
+        hipLaunchKernelGGL(m2_colsum_kernel, dim3(k_tilde), dim3(256), 0, s, vpart, nb, k_tilde, both, 1.0 / n, v);
+        if ((st = check_launch("m2_colsum_kernel")) != OTM_OK) return st;
+        if (d >= 1) {
+            if (CT->nnz >= (int64_t)256 * d)
+                hipLaunchKernelGGL(m2_panel2_kernel<true>, dim3(panel_blocks(d, 1, k_tilde)), dim3(kM2Threads), 0, s, *CT,
+                                   T1, k_tilde, 1.0 / n, O, u, M1);
+            else
+                hipLaunchKernelGGL(m2_panel2_kernel<false>, dim3(panel_blocks(d, kPanelRows, k_tilde)), dim3(kM2Threads),
+                                   0, s, *CT, T1, k_tilde, 1.0 / n, O, u, M1);
+            if ((st = check_launch("m2_panel2_kernel")) != OTM_OK) return st;
+            hipLaunchKernelGGL(m2_epilogue_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, O, S, u, M1, v,
+                               d, k_tilde, (alpha0 + 1.0) / n, alpha0);
+            if ((st = check_launch("m2_epilogue_kernel")) != OTM_OK) return st;
+        }
+        return OTM_OK;
+    }
     double* T1 = wc.take<double>((size_t)n * k_tilde);
     double* w1 = wc.take<double>(n);
     double* w2 = wc.take<double>(n);
@@ -531,10 +787,10 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
     m2_dispatch(k_tilde, at % 16 == 0, [&](auto v2c, auto nuc) {
         constexpr bool V2 = decltype(v2c)::value;
         constexpr int NU = decltype(nuc)::value;
-        hipLaunchKernelGGL((m2_pass1_kernel<V2, NU>), dim3(b1), dim3(kM2Threads), 0, s, *C, normalize, S, k_tilde, T1,
+        hipLaunchKernelGGL((m2_pass1_kernel<V2, NU>), dim3(b1), dim3(kM2Threads), 0, s, *C, normalize, S, k_tilde, k_tilde, T1,
                            w1, w2, vpart, info);
         if ((st = check_launch("m2_pass1_kernel")) != OTM_OK) return;
-        hipLaunchKernelGGL(m2_colsum_kernel, dim3(k_tilde), dim3(256), 0, s, vpart, b1, k_tilde, 1.0 / n, v);
+        hipLaunchKernelGGL(m2_colsum_kernel, dim3(k_tilde), dim3(256), 0, s, vpart, b1, k_tilde, false, 1.0 / n, v);
         if ((st = check_launch("m2_colsum_kernel")) != OTM_OK) return;
         if (!split) {
             hipLaunchKernelGGL((m2_pass2_kernel<V2, NU>), dim3(m2_blocks(d)), dim3(kM2Threads), 0, s, *CT, T1, k_tilde,

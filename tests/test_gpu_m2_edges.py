@@ -57,3 +57,32 @@ def test_m2_apply(m, n, d, heavy, normalize):
     torch.cuda.synchronize()
     assert rel(O.cpu().numpy(), ref) < 1e-12
     assert torch.equal(O, again)             # fixed order of every sum
+
+
+@pytest.mark.parametrize("n,d,m,per_row,normalize",
+                         [(41000, 40500, 50, 6, False), (41000, 40500, 51, 6, True), (42000, 1000, 48, 8, True),
+                          (42000, 40000, 62, 5, True), (64000, 90, 32, 4, True), (20000, 100, 128, 40, False)])
+def test_m2_apply_panels(n, d, m, per_row, normalize):
+    """Matrices past 16 MB: both passes by panels, the second alone, rows of C^T
+    short and long (a workgroup each), m at the ends of a panel with and without room
+    for the two weight columns, empty rows of C^T."""
+    import scipy.sparse as sp
+
+    g = np.random.default_rng(n + m)
+    cols = g.integers(0, d - 1, (n, per_row))         # column d - 1 stays empty
+    C = sp.csr_matrix((g.integers(1, 4, n * per_row).astype(np.float64),
+                       (np.repeat(np.arange(n), per_row), cols.reshape(-1))), shape=(n, d))
+    C.sum_duplicates()
+    S = g.standard_normal((d, m))
+    rs = np.asarray(C.sum(1)).ravel()
+    a1, a2 = (1 / rs, 1 / (rs * (rs - 1))) if normalize else (np.ones(n), np.ones(n))
+    M1 = C.T @ a1 / n
+    ref = 1.7 / n * (C.T @ (a2[:, None] * (C @ S)) - (C.T @ a2)[:, None] * S) - 0.7 * np.outer(M1, M1 @ S)
+    CT = C.T.tocsr()
+    dc = lambda M: _dev_csr(M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data.astype(np.float32), M.shape[1])
+    A, AT, St = dc(C), dc(CT), torch.from_numpy(S).to(dev())
+    O = otm.m2_apply(A, AT, normalize, 0.7, St)
+    again = otm.m2_apply(A, AT, normalize, 0.7, St)
+    torch.cuda.synchronize()
+    assert rel(O.cpu().numpy(), ref) < 1e-12
+    assert torch.equal(O, again)
