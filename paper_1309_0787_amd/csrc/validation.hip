@@ -70,16 +70,17 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __
 
 // partials over node split z: cross[z][i][j] = sum_x (a_ix - abar_i)(b_jx - bbar_j),
 // l1[z][i][j] = sum_x |a_ix - b_jx|.  A thread owns 4 x 4 pairs, so a node costs it
-// two 16-byte LDS reads and 56 FP64 operations (16 x 16 pairs per workgroup, one
-// per thread, took two reads for 4: k_hat = k = 100, n = 50000 282 -> 185 us; the
-// additions and products alone take 60 at full rate).
+// four 16-byte LDS reads and 56 FP64 operations (16 x 16 pairs per workgroup, one
+// per thread, took two reads for 4: k_hat = k = 100, n = 50000 282 -> 169 us; the
+// additions and products alone take 60 at full rate; on the matrix cores the cross
+// sums made it 224).
 __global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict__ Ph, int kh,
                                                          const float* __restrict__ P, int k, int n,
                                                          const double* __restrict__ mean, double* __restrict__ cross,
                                                          double* __restrict__ l1) {
     // node-major; the pitch keeps 16-byte reads aligned
-    __shared__ __attribute__((aligned(16))) float sa[kChunk][kTile + 4];
-    __shared__ __attribute__((aligned(16))) float sb[kChunk][kTile + 4];
+    __shared__ __attribute__((aligned(16))) double sa[kChunk][kTile + 2];
+    __shared__ __attribute__((aligned(16))) double sb[kChunk][kTile + 2];
     const int i0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, z = blockIdx.z;
     const int x0 = z * kNodesPerBlock, x1 = min(n, x0 + kNodesPerBlock);
     const int ti = threadIdx.x / 16 * kPair, tj = threadIdx.x % 16 * kPair;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict
     for (int xb = x0; xb < x1; xb += kChunk) {
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
-            sa[cs][rs + 256 / kChunk * u] = pa[u];
+            sa[cs][rs + 256 / kChunk * u] = pa[u];   // (converted once, not by every thread)
             sb[cs][rs + 256 / kChunk * u] = pb[u];
         }
         __syncthreads();
@@ -116,13 +117,11 @@ __global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict
         const int cnt = live ? min(kChunk, x1 - xb) : 0;
 #pragma unroll 2
         for (int cc = 0; cc < cnt; ++cc) {
-            const f32x4 af = *reinterpret_cast<const f32x4*>(&sa[cc][ti]);
-            const f32x4 bf = *reinterpret_cast<const f32x4*>(&sb[cc][tj]);
             double a[kPair], b[kPair], da[kPair], db[kPair];
 #pragma unroll
             for (int u = 0; u < kPair; ++u) {
-                a[u] = af[u];
-                b[u] = bf[u];
+                a[u] = sa[cc][ti + u];
+                b[u] = sb[cc][tj + u];
                 da[u] = a[u] - ma[u];
                 db[u] = b[u] - mb[u];
             }
