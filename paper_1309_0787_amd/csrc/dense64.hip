@@ -68,7 +68,9 @@ TnShape tn_shape(int d, int p, int q, bool gram) {
 
 __global__ __launch_bounds__(256, 2) void gemm_tn_kernel(const double* __restrict__ A, int lda,
                                                       const double* __restrict__ B, int ldb, int d, int p, int q,
-                                                      TnShape t, bool gram, double* __restrict__ part) {
+                                                      TnShape t, bool gram, double* __restrict__ part,
+                                                      const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     __shared__ f64x4 sacc[kTnT * kTnT][64];
     const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -174,11 +176,12 @@ size_t gemm_tn_ws(int d, int p, int q) {
 }
 
 int gemm_tn(const double* A, int lda, const double* B, int ldb, int d, int p, int q, double* C, double* part,
-            hipStream_t s) {
+            hipStream_t s, const int* run = nullptr) {
     const bool gram = A == B && lda == ldb && p == q;
     const TnShape t = tn_shape(d, p, q, gram);
     double* out = t.nparts > 1 ? part : C;
-    hipLaunchKernelGGL(gemm_tn_kernel, dim3(t.groups, t.nparts), dim3(256), 0, s, A, lda, B, ldb, d, p, q, t, gram, out);
+    hipLaunchKernelGGL(gemm_tn_kernel, dim3(t.groups, t.nparts), dim3(256), 0, s, A, lda, B, ldb, d, p, q, t, gram, out,
+                       run);
     int st = check_launch("gemm_tn_kernel");
     if (st != OTM_OK || t.nparts == 1) return st;
     const int64_t m = (int64_t)p * q;
@@ -198,7 +201,9 @@ int gemm_tn(const double* A, int lda, const double* B, int ldb, int d, int p, in
 // 7.8 -> 4.6.
 template <int MT, int NT>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__ A, int lda, const double* __restrict__ B,
-                                                      int ldb, double* __restrict__ C, int ldc, int d, int p, int q) {
+                                                      int ldb, double* __restrict__ C, int ldc, int d, int p, int q,
+                                                      const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = (blockIdx.x * 4 + w) * MT * 16;
@@ -271,15 +276,15 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__
 }
 
 int gemm_nn(const double* A, int lda, const double* B, int ldb, double* C, int ldc, int d, int p, int q,
-            hipStream_t s) {
+            hipStream_t s, const int* run = nullptr) {
     OTM_REQUIRE(d >= 1 && p >= 1 && q >= 1, OTM_ESHAPE, "gemm_nn needs d, p, q >= 1");
     const int tq = (q + 15) / 16;
     if ((int64_t)((d + 31) / 32) * ((tq + 6) / 7) >= 1024)
         hipLaunchKernelGGL((gemm_nn_kernel<2, 7>), dim3((d + 127) / 128, (tq + 6) / 7), dim3(256), 0, s, A, lda, B, ldb,
-                           C, ldc, d, p, q);
+                           C, ldc, d, p, q, run);
     else
         hipLaunchKernelGGL((gemm_nn_kernel<1, 2>), dim3((d + 63) / 64, (tq + 1) / 2), dim3(256), 0, s, A, lda, B, ldb, C,
-                           ldc, d, p, q);
+                           ldc, d, p, q, run);
     return check_launch("gemm_nn_kernel");
 }
 
@@ -718,12 +723,12 @@ constexpr int kColBlocks = 128;
 // ------------------------------------------- shared with other translation units
 size_t gemm_tn_f64_ws(int d, int p, int q) { return gemm_tn_ws(d, p, q); }
 int gemm_tn_f64(const double* A, int lda, const double* B, int ldb, int d, int p, int q, double* C, double* part,
-                hipStream_t s) {
-    return gemm_tn(A, lda, B, ldb, d, p, q, C, part, s);
+                hipStream_t s, const int* run) {
+    return gemm_tn(A, lda, B, ldb, d, p, q, C, part, s, run);
 }
 int gemm_nn_f64(const double* A, int lda, const double* B, int ldb, double* C, int ldc, int d, int p, int q,
-                hipStream_t s) {
-    return gemm_nn(A, lda, B, ldb, C, ldc, d, p, q, s);
+                hipStream_t s, const int* run) {
+    return gemm_nn(A, lda, B, ldb, C, ldc, d, p, q, s, run);
 }
 
 size_t cholqr2_ws(int d, int m) {
@@ -825,7 +830,8 @@ extern "C" int otm_whitener(const double* O, const double* S, int32_t d, int32_t
     if ((st = gemm_tn(Bm, k, Bm, k, d, k, k, Gr, part, s)) != OTM_OK) return st;
     hipLaunchKernelGGL(symmetrize_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, Gr, k);
     if ((st = check_launch("symmetrize_kernel")) != OTM_OK) return st;
-    if ((st = jacobi(Gr, Vb, k, evb, ordb, jws, s)) != OTM_OK) return st;
+    // (B = O U sigma^(-1/2) has nearly orthogonal columns where S spans an invariant space)
+    if ((st = jacobi(Gr, Vb, k, evb, ordb, jws, s, true)) != OTM_OK) return st;
     hipLaunchKernelGGL(whiten_scale_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, Vb, evb, ordb, k, info, Pw,
                        evals);
     if ((st = check_launch("whiten_scale_kernel")) != OTM_OK) return st;

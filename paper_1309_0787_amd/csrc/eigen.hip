@@ -1,18 +1,19 @@
-// Symmetric eigensolver (FP64) for 48 < n <= 200 without rotations: one pass of
+// Symmetric eigensolver (FP64) for 32 < n <= 200 without rotations: one pass of
 // Householder reflections to tridiagonal form, its eigenvalues by multisection of
 // Sturm counts, its eigenvectors by twisted factorizations, the reflections
-// applied to them, and two steps of iterative refinement on the whole matrix
+// applied to them, and one or two steps of iterative refinement on the whole matrix
 // (Ogita and Aishima, "Iterative refinement for symmetric eigenvalue
 // decomposition", Japan J. Indust. Appl. Math. 35, 2018), which restores
 // eigenvectors and orthogonality to working precision quadratically.  Each step
-// measures its own correction; where the second one is not small enough for that
-// (eigenvalues so close that the twisted factorizations give dependent vectors),
-// *redo is set and the Jacobi solver of jacobi.hip runs instead.
+// measures its own correction: where the first is below 1e-8 it was the last, since what
+// it leaves is its square; where the second is not either (eigenvalues so close that
+// the twisted factorizations give dependent vectors), *redo is set and the Jacobi
+// solver of jacobi.hip runs instead.
 //
 // What bounds it: the reduction is n - 2 dependent steps on one CU (matrix in
 // registers, two barriers a step); everything else is spread over the device but
 // short, so launches and latencies count.  The eigenproblems of a whitener with 200
-// and 100 columns: 8740 us by rotations -> 1300 (the reduction 2 x 363 of it).
+// and 100 columns: 8740 us by rotations -> 1170 (the reduction 2 x 363 of it).
 #include <cfloat>
 #include <cmath>
 
@@ -376,14 +377,16 @@ __global__ __launch_bounds__(64) void reflect_kernel(const double* __restrict__ 
         if (lane + 64 * b < n) X[(size_t)(lane + 64 * b) * n + m] = z[b];
 }
 
-// Of S = X^T A X and G = X^T X: lam_i = S_ii / G_ii, and stat = {threshold under
-// which two eigenvalues count as one, largest |lam|}; with order != NULL also
-// order[j] = index of the j-th largest.
+// Of S = X^T A X and G = X^T X: lam_i = S_ii / G_ii, stat = {threshold under which two
+// eigenvalues count as one, largest |lam|}, order[j] = index of the j-th largest.
+// (This kernel and the next return at once where run points to 0.)
 constexpr int kStatThreads = 1024;
 __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double* __restrict__ S,
                                                                    const double* __restrict__ G, int n,
                                                                    double* __restrict__ lam, double* __restrict__ stat,
-                                                                   int* __restrict__ order) {
+                                                                   int* __restrict__ order, int* __restrict__ flag,
+                                                                   const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     __shared__ double sl[kEigN], red[3][kStatThreads / 64];
     const int tid = threadIdx.x;
     double off = 0.0, orth = 0.0, big = 0.0;
@@ -418,22 +421,24 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
         }
         stat[0] = 2.0 * (sqrt(off) + big * sqrt(orth));
         stat[1] = big;
+        *flag = 0;                                     // for refine_kernel
     }
-    if (order != nullptr)
-        for (int i = tid; i < n; i += kStatThreads) {
-            const double v = sl[i];
-            int rank = 0;
-            for (int j = 0; j < n; ++j) rank += sl[j] > v || (sl[j] == v && j < i);
-            if (rank < n) order[rank] = i;
-        }
+    for (int i = tid; i < n; i += kStatThreads) {
+        const double v = sl[i];
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += sl[j] > v || (sl[j] == v && j < i);
+        if (rank < n) order[rank] = i;
+    }
 }
 
-// E = I + the correction of X; with redo != NULL (the last step) *redo = 1 unless
-// every entry of it is below 1e-8, so that what it leaves is below 1e-16, and the
-// entries between eigenvalues that count as one are rounding errors of S.
+// E = I + the correction of X; *flag = 1 unless every entry of it is below 1e-8, so
+// that what it leaves is below 1e-16, and the entries between eigenvalues that count
+// as one are rounding errors of S.
 __global__ __launch_bounds__(256) void refine_kernel(const double* __restrict__ S, const double* __restrict__ G, int n,
                                                      const double* __restrict__ lam, const double* __restrict__ stat,
-                                                     double* __restrict__ E, int* __restrict__ redo) {
+                                                     double* __restrict__ E, int* __restrict__ flag,
+                                                     const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= n * n) return;
     const int i = e / n, j = e - i * n;
@@ -442,12 +447,19 @@ __global__ __launch_bounds__(256) void refine_kernel(const double* __restrict__ 
     const bool apart = i != j && fabs(gap) > stat[0];
     const double c = apart ? (s + lam[j] * r) / gap : 0.5 * r;
     E[e] = (i == j ? 1.0 : 0.0) + c;
-    if (redo != nullptr && (!(fabs(c) < 1e-8) || (!apart && i != j && !(fabs(s) <= 1e-14 * stat[1])))) *redo = 1;
+    if (!(fabs(c) < 1e-8) || (!apart && i != j && !(fabs(s) <= 1e-14 * stat[1]))) *flag = 1;
+}
+
+// V = U where *run is not 0
+__global__ __launch_bounds__(256) void copy_if_kernel(const double* __restrict__ U, int count, double* __restrict__ V,
+                                                      const int* __restrict__ run) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (*run != 0 && e < count) V[e] = U[e];
 }
 
 }  // namespace
 
-bool eigen_direct_takes(int n) { return n > 48 && n <= kEigN; }
+bool eigen_direct_takes(int n) { return n > 32 && n <= kEigN; }
 
 size_t eigen_direct_ws(int n) {
     return 6 * ws_round(sizeof(double) * (size_t)n * n) + 5 * ws_round(sizeof(double) * n);
@@ -469,20 +481,26 @@ int eigen_direct(const double* A, double* V, int n, double* evals, int* order, i
     if ((st = check_launch("twisted_kernel")) != OTM_OK) return st;
     hipLaunchKernelGGL(reflect_kernel, dim3(n), dim3(64), 0, s, U, rh, n, Z, X);
     if ((st = check_launch("reflect_kernel")) != OTM_OK) return st;
-    for (int step = 0; step < 2; ++step) {             // X -> U -> V
-        const double* from = step == 0 ? X : U;
-        double* to = step == 0 ? U : V;
-        if ((st = gemm_nn_f64(A, n, from, n, Z, n, n, n, n, s)) != OTM_OK) return st;
-        if ((st = gemm_tn_f64(from, n, Z, n, n, n, n, S, E, s)) != OTM_OK) return st;
-        if ((st = gemm_tn_f64(from, n, from, n, n, n, n, G, E, s)) != OTM_OK) return st;
-        hipLaunchKernelGGL(refine_stat_kernel, dim3(1), dim3(kStatThreads), 0, s, S, G, n, step == 0 ? lam : evals, stat,
-                           step == 0 ? nullptr : order);
+    // X -> V; where that correction was not small enough to be the last, V -> U -> V
+    int* more = reinterpret_cast<int*>(stat + 2);
+    for (int step = 0; step < 2; ++step) {
+        const double* from = step == 0 ? X : V;
+        double* to = step == 0 ? V : U;
+        const int* again = step == 0 ? nullptr : more;
+        if ((st = gemm_nn_f64(A, n, from, n, Z, n, n, n, n, s, again)) != OTM_OK) return st;
+        if ((st = gemm_tn_f64(from, n, Z, n, n, n, n, S, E, s, again)) != OTM_OK) return st;
+        if ((st = gemm_tn_f64(from, n, from, n, n, n, n, G, E, s, again)) != OTM_OK) return st;
+        hipLaunchKernelGGL(refine_stat_kernel, dim3(1), dim3(kStatThreads), 0, s, S, G, n, evals, stat, order,
+                           step == 0 ? more : redo, again);
         if ((st = check_launch("refine_stat_kernel")) != OTM_OK) return st;
-        hipLaunchKernelGGL(refine_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, S, G, n,
-                           step == 0 ? lam : evals, stat, E, step == 0 ? nullptr : redo);
+        hipLaunchKernelGGL(refine_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, S, G, n, evals, stat, E,
+                           step == 0 ? more : redo, again);
         if ((st = check_launch("refine_kernel")) != OTM_OK) return st;
-        if ((st = gemm_nn_f64(from, n, E, n, to, n, n, n, n, s)) != OTM_OK) return st;
+        if ((st = gemm_nn_f64(from, n, E, n, to, n, n, n, n, s, again)) != OTM_OK) return st;
     }
+    hipLaunchKernelGGL(copy_if_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, U, static_cast<int>(nn), V,
+                       more);
+    if ((st = check_launch("copy_if_kernel")) != OTM_OK) return st;
     return OTM_OK;
 }
 

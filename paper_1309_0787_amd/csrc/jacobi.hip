@@ -26,6 +26,7 @@ namespace {
 constexpr int kJacThreads = 1024;
 constexpr int kJacMaxN = 256;
 constexpr int kJacLdsN = 200;
+constexpr int kJacSmallN = 32;
 constexpr int kJacMaxSweeps = 60;
 
 __device__ __forceinline__ int rr_player(int pos, int round, int N) {
@@ -54,22 +55,23 @@ __device__ __forceinline__ int roff(int i, int n) { return i * n - (i * (i - 1))
 // Returns at once where run points to 0 (so does the replay).
 // log_rot[round * npairs + slot], log_pq[round * npairs + slot] = p | q << 16;
 // *rounds = number of rounds performed.
-__global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* __restrict__ Ain, int n,
+template <int THREADS, int N>
+__global__ __launch_bounds__(THREADS) void jacobi_lds_kernel(const double* __restrict__ Ain, int n,
                                                                  double* __restrict__ evals, int* __restrict__ order,
                                                                  Rot* __restrict__ log_rot, int* __restrict__ log_pq,
                                                                  int* __restrict__ rounds,
                                                                  const int* __restrict__ run) {
     if (run != nullptr && *run == 0) return;
-    __shared__ double sA[kJacLdsN * (kJacLdsN + 1) / 2];
-    __shared__ Rot srot[kJacLdsN / 2];
-    __shared__ PairSlot spq[kJacLdsN / 2];
-    __shared__ double s_red[kJacThreads / 64];
+    __shared__ double sA[N * (N + 1) / 2];
+    __shared__ Rot srot[N / 2];
+    __shared__ PairSlot spq[N / 2];
+    __shared__ double s_red[THREADS / 64];
     __shared__ int s_rotated;
     const int tid = threadIdx.x;
-    const int N = (n + 1) & ~1;
-    const int npairs = N / 2;
+    const int players = (n + 1) & ~1;
+    const int npairs = players / 2;
     double f = 0.0;
-    for (int e = tid; e < n * n; e += kJacThreads) {
+    for (int e = tid; e < n * n; e += THREADS) {
         const int i = e / n, j = e % n;
         const double a = Ain[e];
         f += a * a;
@@ -79,17 +81,17 @@ __global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* _
     if ((tid & 63) == 0) s_red[tid >> 6] = f;
     __syncthreads();
     double fro = 0.0;
-    for (int w = 0; w < kJacThreads / 64; ++w) fro += s_red[w];
+    for (int w = 0; w < THREADS / 64; ++w) fro += s_red[w];
     const double abs_tol = 1e-15 * sqrt(fro);
     // static list of this thread's off-diagonal blocks (pair slots P < Q);
     // the diagonal block of a pair is rotated by the thread that computes
     // its rotation
-    constexpr int kBlk = 5;   // 100 * 99 / 2 <= 5 * 1024
+    constexpr int kBlk = (N / 2 * (N / 2 - 1) / 2 + THREADS - 1) / THREADS;
     int blkP[kBlk], blkQ[kBlk];
     const int nblk = npairs * (npairs - 1) / 2;
 #pragma unroll
     for (int j = 0; j < kBlk; ++j) {
-        int e = tid + j * kJacThreads, P = -1, Q = -1;
+        int e = tid + j * THREADS, P = -1, Q = -1;
         if (e < nblk) {
             P = 0;
             while (e >= npairs - 1 - P) { e -= npairs - 1 - P; ++P; }
@@ -103,9 +105,9 @@ __global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* _
     for (int sweep = 0; sweep < kJacMaxSweeps; ++sweep) {
         if (tid == 0) s_rotated = 0;
         __syncthreads();
-        for (int round = 0; round < N - 1; ++round) {
+        for (int round = 0; round < players - 1; ++round) {
             if (tid < npairs) {
-                int p = rr_player(tid, round, N), q = rr_player(N - 1 - tid, round, N);
+                int p = rr_player(tid, round, players), q = rr_player(players - 1 - tid, round, players);
                 if (p > q) { const int t = p; p = q; q = t; }
                 double c = 1.0, s = 0.0;
                 const int rp = roff(p, n), rq = roff(q, n);
@@ -163,14 +165,14 @@ __global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* _
             }
             __syncthreads();
         }
-        done_rounds += N - 1;
+        done_rounds += players - 1;
         if (!s_rotated) break;
         // converged when no pair passes the rotation test: the next sweep
         // would leave A as it is, so it is not run
         __syncthreads();
         if (tid == 0) s_rotated = 0;
         __syncthreads();
-        for (int e = tid; e < n * n; e += kJacThreads) {
+        for (int e = tid; e < n * n; e += THREADS) {
             const int i = e / n, j = e - (e / n) * n;
             if (i < j) {
                 const double aij = sA[tri_idx(i, j, n)];
@@ -183,9 +185,9 @@ __global__ __launch_bounds__(kJacThreads) void jacobi_lds_kernel(const double* _
         __syncthreads();
     }
     if (tid == 0) *rounds = done_rounds;
-    for (int i = tid; i < n; i += kJacThreads) evals[i] = sA[tri_idx(i, i, n)];
+    for (int i = tid; i < n; i += THREADS) evals[i] = sA[tri_idx(i, i, n)];
     __syncthreads();
-    for (int i = tid; i < n; i += kJacThreads) {
+    for (int i = tid; i < n; i += THREADS) {
         const double v = evals[i];
         int rank = 0;
         for (int j = 0; j < n; ++j) {
@@ -368,7 +370,7 @@ size_t jacobi_ws_bytes(int n) {
            (eigen_direct_takes(n) ? eigen_direct_ws(n) : 0);
 }
 
-int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s) {
+int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s, bool near_diagonal) {
     if (n < 1 || n > kJacMaxN) return fail(OTM_ECAPACITY, "eigensolver size must be in [1, 256]");
     if (n <= kJacLdsN) {
         WsCarver wc(ws, jacobi_ws_bytes(n));
@@ -376,16 +378,24 @@ int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hip
         int* lp = wc.take<int>(log_entries(n));
         int* rounds = wc.take<int>(1);
         int* redo = nullptr;
-        // From 49 on the direct solver is the faster one (a whitener with kt = 48 or 49
-        // columns, all of it: 656 us by rotations, 364 direct; at kt = 24, k = 12 the
-        // two are even); the rotations run where it says so
-        if (eigen_direct_takes(n)) {
+        // From 33 on the direct solver is the faster one (a whitener with kt = 40, k = 20,
+        // all of it: 471 us by rotations, 266 with the larger problem direct; kt = 48, k =
+        // 24 656, 297; kt = 32 367, even).  A matrix that is nearly diagonal takes few
+        // sweeps: there it pays from 65 on (kt = 80, k = 40 444 with the Gram of 40 by
+        // rotations, 572 direct).  The rotations run where the direct solver says so.
+        if (eigen_direct_takes(n) && (!near_diagonal || n > 64)) {
             redo = wc.take<int>(1);
             int st = eigen_direct(A, V, n, evals, order, redo, wc.take<char>(eigen_direct_ws(n)), s);
             if (st != OTM_OK) return st;
         }
-        hipLaunchKernelGGL(jacobi_lds_kernel, dim3(1), dim3(kJacThreads), 0, s, A, n, evals, order, lr, lp, rounds,
-                           redo);
+        // (a round of a small matrix is mostly its two barriers: 4 waves meet sooner
+        // than 16; n = 20 and n = 10 together 144 -> 136 us, n = 48 slower)
+        if (n <= kJacSmallN)
+            hipLaunchKernelGGL((jacobi_lds_kernel<256, kJacSmallN>), dim3(1), dim3(256), 0, s, A, n, evals, order, lr, lp,
+                               rounds, redo);
+        else
+            hipLaunchKernelGGL((jacobi_lds_kernel<kJacThreads, kJacLdsN>), dim3(1), dim3(kJacThreads), 0, s, A, n, evals,
+                               order, lr, lp, rounds, redo);
         int st = check_launch("jacobi_lds_kernel");
         if (st != OTM_OK) return st;
         hipLaunchKernelGGL(jacobi_apply_kernel, dim3((n + kRowsPerWg - 1) / kRowsPerWg), dim3(kApplyThreads), 0, s, lr,

@@ -46,8 +46,10 @@ int validate_csr_header(const otm_csr* C, const char* name);
 // Symmetric FP64 eigensolver for n <= 256 (jacobi.hip): A (n x n, overwritten),
 // V (n x n, eigenvectors as columns), evals[i] = eigenvalue of column i,
 // order[j] = column of the j-th largest eigenvalue.  ws: jacobi_ws_bytes(n).
+// near_diagonal says what to expect of A, for the choice of the method only.
 size_t jacobi_ws_bytes(int n);
-int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s);
+int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s,
+           bool near_diagonal = false);
 
 // The same without rotations (eigen.hip), for the n it takes: V, evals, order as
 // above, A kept; *redo = 1 where they are not to working precision.
@@ -57,12 +59,13 @@ int eigen_direct(const double* A, double* V, int n, double* evals, int* order, i
 
 // FP64 dense products (dense64.hip): C (p x q) = A^T B for tall A (d x p),
 // B (d x q), split over row chunks into `part` (gemm_tn_f64_ws bytes), then a
-// fixed-order reduction; C (d x q) = A B for tall A (d x p), small B (p x q).
+// fixed-order reduction; C (d x q) = A B for tall A (d x p), small B (p x q).  Where
+// run is given and points to 0 on the device nothing is computed (d <= 256 only).
 size_t gemm_tn_f64_ws(int d, int p, int q);
 int gemm_tn_f64(const double* A, int lda, const double* B, int ldb, int d, int p, int q, double* C, double* part,
-                hipStream_t s);
+                hipStream_t s, const int* run = nullptr);
 int gemm_nn_f64(const double* A, int lda, const double* B, int ldb, double* C, int ldc, int d, int p, int q,
-                hipStream_t s);
+                hipStream_t s, const int* run = nullptr);
 // Cholesky QR applied twice (m <= 200): Q (d x m) orthonormal with Y = Q R,
 // and Rinv = R^-1 (m x m, upper triangular).  info as in otm_orthonormalize.
 size_t cholqr2_ws(int d, int m);

@@ -1,5 +1,5 @@
-"""The eigensolver behind the whitener at the sizes where its path changes (48 and
-49, the 64-column blocks, 200 and 201) and on spectra that its direct form must hand
+"""The eigensolver behind the whitener at the sizes where its path changes (32 and
+33, 64 and 65, the 64-column blocks, 200 and 201) and on spectra that its direct form must hand
 to the rotations (equal and nearly equal eigenvalues) or meets as they are (blocks
 that do not couple, a diagonal matrix): Omega = S^T O with S orthonormal and O = S M,
 M symmetric positive definite of kt x kt, so the whitener's eigenvalues are M's.
@@ -38,7 +38,7 @@ def _matrix(kt, kind, g):
     return 0.5 * (M + M.T)
 
 
-@pytest.mark.parametrize("kt", [48, 49, 64, 65, 100, 128, 129, 192, 193, 200, 201])
+@pytest.mark.parametrize("kt", [20, 32, 33, 48, 64, 65, 100, 128, 129, 192, 193, 200, 201])
 @pytest.mark.parametrize("kind", ["spread", "close", "equal", "diagonal", "blocks"])
 def test_whitener_spectra(kt, kind):
     g = np.random.default_rng(kt)
