@@ -533,31 +533,32 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T* __restrict__ A, int 
 // 144 floats apart.  Global reads are 16 bytes wide, the next block's in flight while
 // this one is multiplied, and LDS holds two blocks (one barrier each).  Batch 256,
 // before (the kernel above: 4-byte loads, waited for before every block) and after,
-// us: forward 402 -> 163 for the two products, backward 328 -> 203 for three (29
-// GFLOP in all, 79 TFLOP/s of the 133 that a large FP32 product reaches here).
-constexpr int WBM = 128, WBK = 16, WPK = WBK + 4, WPM = WBM + 16;
+// us: forward 402 -> 157 for the two products, backward 328 -> 189 for three (29
+// GFLOP in all, 84 TFLOP/s of the 133 that a large FP32 product reaches here).
+constexpr int WBM = 128, WBK = 16, WPK = WBK + 4;
 
 // One operand of the tile: rows x0 .. x0 + 127 of its M (N) side, contiguous along k
 // (T = false) or along that side (T = true), L elements from one row to the next.
-template <bool T>
+template <bool T, int X>
 struct WideOperand {
-    static constexpr int kFloats = T ? WBK * WPM : WBM * WPK;
-    f32x4 r[2];
-    __device__ void load(const float* __restrict__ X, int L, int x0, int nx, int k0, int ke, int tid) {
+    static constexpr int kPitch = X + 16, kLoads = X / 64;
+    static constexpr int kFloats = T ? WBK * kPitch : X * WPK;
+    f32x4 r[kLoads];
+    __device__ void load(const float* __restrict__ P, int L, int x0, int nx, int k0, int ke, int tid) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kLoads; ++u) {
             const int e = tid + 256 * u;
-            const int x = x0 + (T ? 4 * (e & 31) : e >> 2), k = k0 + (T ? e >> 5 : 4 * (e & 3));
+            const int x = x0 + (T ? 4 * (e % (X / 4)) : e >> 2), k = k0 + (T ? e / (X / 4) : 4 * (e & 3));
             r[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (x < nx && k < ke) r[u] = *reinterpret_cast<const f32x4*>(X + (T ? (size_t)k * L + x : (size_t)x * L + k));
+            if (x < nx && k < ke) r[u] = *reinterpret_cast<const f32x4*>(P + (T ? (size_t)k * L + x : (size_t)x * L + k));
         }
     }
     __device__ void store(float* __restrict__ lds, int tid) const {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kLoads; ++u) {
             const int e = tid + 256 * u;
             if constexpr (T) {
-                *reinterpret_cast<f32x4*>(lds + (e >> 5) * WPM + 4 * (e & 31)) = r[u];
+                *reinterpret_cast<f32x4*>(lds + e / (X / 4) * kPitch + 4 * (e % (X / 4))) = r[u];
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) lds[(e >> 2) * WPK + 4 * q + (e & 3)] = r[u][q];
@@ -567,34 +568,35 @@ struct WideOperand {
     // k = 4 e + q, e < 4, of row x
     __device__ static f32x4 frag(const float* __restrict__ lds, int x, int q) {
         if constexpr (T) {
-            const float* p = lds + q * WPM + x;
-            return f32x4{p[0], p[4 * WPM], p[8 * WPM], p[12 * WPM]};
+            const float* p = lds + q * kPitch + x;
+            return f32x4{p[0], p[4 * kPitch], p[8 * kPitch], p[12 * kPitch]};
         } else {
             return *reinterpret_cast<const f32x4*>(lds + x * WPK + 4 * q);
         }
     }
 };
 
-template <bool TA, bool TB>
+template <bool TA, bool TB, int WBN>
 __global__ __launch_bounds__(256) void gemm_wide_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B,
                                                         int ldb, float* __restrict__ C, int ldc, int M, int N, int K,
                                                         int kc, const float* __restrict__ bias, int relu,
                                                         float* __restrict__ part) {
-    using OA = WideOperand<TA>;
-    using OB = WideOperand<!TB>;
+    constexpr int NJ = WBN / 32;                       // column tiles per wave
+    using OA = WideOperand<TA, WBM>;
+    using OB = WideOperand<!TB, WBN>;
     __shared__ __attribute__((aligned(16))) float As[2][OA::kFloats];
     __shared__ __attribute__((aligned(16))) float Bs[2][OB::kFloats];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
-    const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
+    const int wm = (w >> 1) * 64, wn = (w & 1) * (WBN / 2);
     const int l16 = lane & 15, qd = lane >> 4;
-    const int m0 = blockIdx.y * WBM, n0 = blockIdx.x * WBM;
+    const int m0 = blockIdx.y * WBM, n0 = blockIdx.x * WBN;
     const int kb = blockIdx.z * kc, ke = min(K, kb + kc);
-    f32x4 acc[4][4];
+    f32x4 acc[4][NJ];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     OA a;
     OB b;
     a.load(A, lda, m0, M, kb, ke, tid);
@@ -609,18 +611,17 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const float* __restrict_
             a.load(A, lda, m0, M, k0 + WBK, ke, tid);
             b.load(B, ldb, n0, N, k0 + WBK, ke, tid);
         }
-        f32x4 fa[4], fb[4];
+        f32x4 fa[4], fb[NJ];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            fa[i] = OA::frag(As[cur], wm + i * 16 + l16, qd);
-            fb[i] = OB::frag(Bs[cur], wn + i * 16 + l16, qd);
-        }
+        for (int i = 0; i < 4; ++i) fa[i] = OA::frag(As[cur], wm + i * 16 + l16, qd);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) fb[j] = OB::frag(Bs[cur], wn + j * 16 + l16, qd);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = MmaT<float>::mma(fa[i][e], fb[j][e], acc[i][j]);
+                for (int j = 0; j < NJ; ++j) acc[i][j] = MmaT<float>::mma(fa[i][e], fb[j][e], acc[i][j]);
         if (more) {
             a.store(As[cur ^ 1], tid);
             b.store(Bs[cur ^ 1], tid);
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const float* __restrict_
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int gm = m0 + wm + i * 16 + 4 * qd + r;
@@ -686,8 +687,10 @@ int gemm(const T* A, int lda, const T* B, int ldb, float* C, int ldc, int M, int
     const bool wide = std::is_same_v<T, float> && M >= 96 && N >= 96 && lda % 4 == 0 && ldb % 4 == 0 &&
                       (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0 &&
                       ((TA && !TB) || K % 4 == 0) && (!TA || M % 4 == 0) && (TB || N % 4 == 0);
-    const int bm = wide ? WBM : GBM;
-    dim3 grid((N + bm - 1) / bm, (M + bm - 1) / bm, splits);
+    // (a wide grid under two workgroups per CU takes half as wide a tile)
+    const bool half = wide && (int64_t)((N + WBM - 1) / WBM) * ((M + WBM - 1) / WBM) * splits < 512;
+    const int bm = wide ? WBM : GBM, bn = half ? WBM / 2 : bm;
+    dim3 grid((N + bn - 1) / bn, (M + bm - 1) / bm, splits);
     const bool direct = splits == 1 && mask == nullptr;   // a mask is applied by the reduction
     OTM_REQUIRE(direct || (ws != nullptr && ws_bytes >= sizeof(float) * (size_t)splits * M * N), OTM_EWORKSPACE,
                 "GEMM workspace too small");
@@ -695,8 +698,11 @@ int gemm(const T* A, int lda, const T* B, int ldb, float* C, int ldc, int M, int
     const int relu0 = direct ? relu : 0;
     float* part = direct ? nullptr : ws;
     if constexpr (std::is_same_v<T, float>) {
-        if (wide)
-            hipLaunchKernelGGL((gemm_wide_kernel<TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc, b0,
+        if (half)
+            hipLaunchKernelGGL((gemm_wide_kernel<TA, TB, WBM / 2>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K,
+                               kc, b0, relu0, part);
+        else if (wide)
+            hipLaunchKernelGGL((gemm_wide_kernel<TA, TB, WBM>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kc, b0,
                                relu0, part);
     }
     if (!wide)
@@ -745,15 +751,16 @@ __global__ void to_bf16_kernel(const float* __restrict__ x, __bf16* __restrict__
 
 // per instance: squared error over the live k x k block (FP64 partial), and
 // dout = 2 (out - target) mask / count
-__global__ void mse_kernel(const int32_t* __restrict__ ks, int count, const float* __restrict__ out,
+constexpr int kMseThreads = 1024;
+__global__ __launch_bounds__(kMseThreads) void mse_kernel(const int32_t* __restrict__ ks, int count, const float* __restrict__ out,
                            const float* __restrict__ tgt, double inv_cnt, float* __restrict__ dout,
                            double* __restrict__ per) {
-    __shared__ double red[256];
+    __shared__ double red[kMseThreads];
     const int inst = blockIdx.x, tid = threadIdx.x;
     const int k = ks[inst];
     double s = 0.0;
 #pragma unroll 4
-    for (int e = tid; e < kOut; e += 256) {
+    for (int e = tid; e < kOut; e += kMseThreads) {
         const int i = e / kP, j = e % kP;
         const bool live = i < k && j < k;
         const size_t idx = (size_t)inst * kOut + e;
@@ -763,7 +770,7 @@ __global__ void mse_kernel(const int32_t* __restrict__ ks, int count, const floa
     }
     red[tid] = s;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
+    for (int h = kMseThreads / 2; h > 0; h >>= 1) {
         if (tid < h) red[tid] += red[tid + h];
         __syncthreads();
     }
@@ -1001,7 +1008,7 @@ extern "C" int otm_ws_mse(int32_t count, const int32_t* ks, int64_t live, const 
     OTM_REQUIRE(ws != nullptr && ws_bytes >= otm_ws_mse_workspace(count), OTM_EWORKSPACE, "loss workspace too small");
     hipStream_t st = as_stream(stream);
     const double inv = 1.0 / static_cast<double>(live);
-    hipLaunchKernelGGL(mse_kernel, dim3(count), dim3(256), 0, st, ks, count, out, target, inv, dout,
+    hipLaunchKernelGGL(mse_kernel, dim3(count), dim3(kMseThreads), 0, st, ks, count, out, target, inv, dout,
                        static_cast<double*>(ws));
     int s = check_launch("mse_kernel");
     if (s != OTM_OK) return s;
