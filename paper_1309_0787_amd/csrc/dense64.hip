@@ -3,8 +3,8 @@
 //  * gemm_tn: C = A^T B for tall A, B (d x p, d x q): partial products over row
 //    ranges, then a fixed-order reduction.
 //  * gemm_nn: C = A B with A tall (d x p) and B small (p x q).
-//  * eigenproblems of the small symmetric matrices go to the Jacobi solver of
-//    jacobi.hip.
+//  * eigenproblems of the small symmetric matrices go to the solvers of jacobi.hip
+//    (rotations) and eigen.hip (direct).
 //  * whitener (Section 3.1; Section 4.2, randomized tall-thin SVD with the
 //    projected matrix truncated to its top k eigenpairs):
 //      Omega = sym(S^T O) -> eig -> B = O U_k sigma_k^(-1/2)
@@ -195,21 +195,26 @@ int gemm_tn(const double* A, int lda, const double* B, int ldb, int d, int p, in
 // (each row's piece is 128 contiguous bytes), so instruction e of a block takes
 // k = k0 + 4 (l / 16) + e from both operands.  MT = 2, NT = 7: B is read once for
 // 32 rows (8 bytes a cycle and CU from L2).  Products with fewer than 1024 such
-// waves take MT = 1, NT = 2: more and shorter chains.  Before and after, us (64 x
+// waves take MT = 1, NT = 2: more and shorter chains.  upper: B is upper triangular
+// (R^-1 of a Cholesky, 50000 x 200 x 200: 107 -> 73), and a column tile ends its
+// contraction at its diagonal tile, the columns with the most work first.  (A row
+// of A that is not finite makes the Gram, and so R^-1, report it.)  Before and after, us (64 x
 // 64 FMA tiles staged in LDS before): 50000 x 200 x 200 206 -> 107 (the matrix cores
 // need 58), 50000 x 200 x 100 97 -> 49, 10000 x 100 x 100 30 -> 14, 1000 x 20 x 20
 // 7.8 -> 4.6.
 template <int MT, int NT>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__ A, int lda, const double* __restrict__ B,
                                                       int ldb, double* __restrict__ C, int ldc, int d, int p, int q,
-                                                      const int* __restrict__ run) {
+                                                      bool upper, const int* __restrict__ run) {
     if (run != nullptr && *run == 0) return;
     const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = (blockIdx.x * 4 + w) * MT * 16;
     if (r0 >= d) return;
     const int tq = (q + 15) / 16;
-    const int j0 = blockIdx.y * tq / gridDim.y, nj = (blockIdx.y + 1) * tq / gridDim.y - j0;
+    const int by = gridDim.y - 1 - blockIdx.y;   // upper: the long contractions first
+    const int j0 = by * tq / gridDim.y, nj = (by + 1) * tq / gridDim.y - j0;
+    const int kend = upper ? min(p, (j0 + nj) * 16) : p;
     f64x4 acc[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -250,6 +255,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__
     load_b(0, 0, 0);
     auto block = [&](int s, int k0) {
         load_a(s ^ 1, k0 + 16);
+        const int jlo = upper ? k0 / 16 - j0 : 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             load_b((e + 1) & 1, e == 3 ? k0 + 16 : k0, (e + 1) & 3);
@@ -257,12 +263,12 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__
             for (int j = 0; j < NT; ++j)
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-                    if (j < nj) acc[i][j] = mma64(a[s][i][e], b[e & 1][j], acc[i][j]);
+                    if (j >= jlo && j < nj) acc[i][j] = mma64(a[s][i][e], b[e & 1][j], acc[i][j]);
         }
     };
-    for (int k0 = 0; k0 < p; k0 += 32) {
+    for (int k0 = 0; k0 < kend; k0 += 32) {
         block(0, k0);
-        if (k0 + 16 < p) block(1, k0 + 16);
+        if (k0 + 16 < kend) block(1, k0 + 16);
     }
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -276,15 +282,15 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const double* __restrict__
 }
 
 int gemm_nn(const double* A, int lda, const double* B, int ldb, double* C, int ldc, int d, int p, int q,
-            hipStream_t s, const int* run = nullptr) {
+            hipStream_t s, const int* run = nullptr, bool upper = false) {
     OTM_REQUIRE(d >= 1 && p >= 1 && q >= 1, OTM_ESHAPE, "gemm_nn needs d, p, q >= 1");
     const int tq = (q + 15) / 16;
     if ((int64_t)((d + 31) / 32) * ((tq + 6) / 7) >= 1024)
         hipLaunchKernelGGL((gemm_nn_kernel<2, 7>), dim3((d + 127) / 128, (tq + 6) / 7), dim3(256), 0, s, A, lda, B, ldb,
-                           C, ldc, d, p, q, run);
+                           C, ldc, d, p, q, upper, run);
     else
         hipLaunchKernelGGL((gemm_nn_kernel<1, 2>), dim3((d + 63) / 64, (tq + 1) / 2), dim3(256), 0, s, A, lda, B, ldb, C,
-                           ldc, d, p, q, run);
+                           ldc, d, p, q, upper, run);
     return check_launch("gemm_nn_kernel");
 }
 
@@ -754,7 +760,7 @@ int cholqr2(const double* Y, int d, int m, double* Q, double* Rinv, int32_t* inf
         if ((st = gemm_tn(src, m, src, m, d, m, m, Gr, part, s)) != OTM_OK) return st;
         hipLaunchKernelGGL(chol_rinv_kernel, dim3(1), dim3(kCholThreads), 0, s, Gr, m, Ri, info, pass);
         if ((st = check_launch("chol_rinv_kernel")) != OTM_OK) return st;
-        if ((st = gemm_nn(src, m, Ri, m, dst, m, d, m, m, s)) != OTM_OK) return st;
+        if ((st = gemm_nn(src, m, Ri, m, dst, m, d, m, m, s, nullptr, true)) != OTM_OK) return st;
         src = Q1;
     }
     // Y = Q R2 R1, so R^-1 = R1^-1 R2^-1
@@ -883,7 +889,7 @@ extern "C" int otm_orthonormalize(const double* Y, int32_t d, int32_t m, double*
             if ((st = gemm_tn(src, m, src, m, d, m, m, Gr, part, s)) != OTM_OK) return st;
             hipLaunchKernelGGL(chol_rinv_kernel, dim3(1), dim3(kCholThreads), 0, s, Gr, m, V, info, pass);
             if ((st = check_launch("chol_rinv_kernel")) != OTM_OK) return st;
-            if ((st = gemm_nn(src, m, V, m, dst, m, d, m, m, s)) != OTM_OK) return st;
+            if ((st = gemm_nn(src, m, V, m, dst, m, d, m, m, s, nullptr, true)) != OTM_OK) return st;
             src = Q1;
         }
         return OTM_OK;
