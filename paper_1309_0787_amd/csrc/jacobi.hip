@@ -1,6 +1,9 @@
 // Symmetric eigensolver (FP64) for the small matrices of the whitening step:
 // the projected moment Omega (k_tilde x k_tilde), the Gram of B (k x k) and
 // the Gram of a sketch (m x m), all at most 256 x 256.
+// From 33 to 200 columns the direct solver of eigen.hip takes them, except a
+// near-diagonal matrix of at most 64, which few sweeps solve; these kernels are
+// launched there too and run only where the device flag of that solver says so.
 //
 // Cyclic two-sided Jacobi in one workgroup.  Rounds follow the round-robin
 // tournament order, so each round applies n/2 disjoint rotations at once:
