@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kM2Threads) void m2_join_kernel(otm_csr CT, int m, 
 // the panel: workgroup 8 s + x runs on XCD x and takes the s-th piece of that XCD's
 // share of the panels in order.  A wave takes a row's entries eight at a time, eight
 // lanes each.  n = d = 50000, nnz = 3.7e6, m = 200: first pass 806 -> 469 us and 31 to pad
-// S, second 867 -> 459 and 52 for the epilogue (12.6 TB/s of gathers; documents, d =
+// S, second 867 -> 495 (12.6 TB/s of gathers; documents, d =
 // 10000, nnz = 1.9e7, m = 100, T1 of 80 MB: second 2345 -> 1638).
 constexpr int kPanel = 16;
 constexpr int kXcds = 8;
@@ -437,14 +437,19 @@ __global__ __launch_bounds__(kM2Threads) void m2_panel1_kernel(otm_csr C, int no
     }
 }
 
-// the sums of the second pass by panels: O = C^T T1, u and M1 from its columns m, m + 1;
-// a wave per row, or (LONG) the four waves of a workgroup on each of its rows
-template <bool LONG>
-__global__ __launch_bounds__(kM2Threads) void m2_panel2_kernel(otm_csr CT, const double* __restrict__ T1, int m,
-                                                               double inv_n, double* __restrict__ O,
-                                                               double* __restrict__ u, double* __restrict__ M1) {
+// The second pass by panels: a wave per row, or (LONG) the four waves of a workgroup
+// on each of its rows.  UNIT: all weights are 1, so u and M1 are the sum of the
+// row's values, which every panel has, and the row is ended here (S ldS apart);
+// otherwise this leaves O = C^T T1 and u, M1 from its columns m, m + 1.  (Graph as
+// above: 459 us and 52 for the epilogue kernel -> 495; with the loads of S and v
+// before the gathers 499, six waves a SIMD for seven.)
+template <bool LONG, bool UNIT>
+__global__ __launch_bounds__(kM2Threads) void m2_panel2_kernel(otm_csr CT, const double* __restrict__ T1, int m, M2End E,
+                                                               int ldS, double* __restrict__ u,
+                                                               double* __restrict__ M1) {
     constexpr int kRows = LONG ? 1 : kPanelRows;
     __shared__ f64x2 sv[kM2Waves][8];
+    __shared__ double su[kM2Waves];
     int panel, row0, piece;
     if (!panel_piece(CT.n_rows, kRows, m, panel, row0, piece)) return;
     const int lane = threadIdx.x & 63, group = lane >> 3, pitch = panel_count(m) * kPanel;
@@ -459,18 +464,25 @@ __global__ __launch_bounds__(kM2Threads) void m2_panel2_kernel(otm_csr CT, const
         panel_gather(CT, b, e, T1 + col, pitch, group, acc, vals, LONG ? w : 0, LONG ? kM2Waves : 1);
         acc[0] = sum_groups(acc[0]);
         acc[1] = sum_groups(acc[1]);
+        if constexpr (UNIT) vals = wave_sum(vals);
         if constexpr (LONG) {
             if (group == 0) sv[w][lane] = acc;
+            if (UNIT && lane == 0) su[w] = vals;
             __syncthreads();
             if (threadIdx.x >= 8) return;
             acc = (sv[0][lane] + sv[1][lane]) + (sv[2][lane] + sv[3][lane]);
+            if constexpr (UNIT) vals = (su[0] + su[1]) + (su[2] + su[3]);
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             if (group != 0) continue;
-            if (col + q < m) O[(size_t)row * m + col + q] = acc[q];
+            if constexpr (UNIT) {
+                if (col + q < m)
+                    E.O[(size_t)row * m + col + q] = E.scale * (acc[q] - vals * E.S[(size_t)row * ldS + col + q]) -
+                                                     E.alpha0 * (vals * E.inv_n) * E.v[col + q];
+            } else if (col + q < m) E.O[(size_t)row * m + col + q] = acc[q];
             else if (col + q == m) u[row] = acc[q];
-            else if (col + q == m + 1) M1[row] = acc[q] * inv_n;
+            else if (col + q == m + 1) M1[row] = acc[q] * E.inv_n;
         }
     }
 }
@@ -753,16 +765,23 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
         hipLaunchKernelGGL(m2_colsum_kernel, dim3(k_tilde), dim3(256), 0, s, vpart, nb, k_tilde, both, 1.0 / n, v);
         if ((st = check_launch("m2_colsum_kernel")) != OTM_OK) return st;
         if (d >= 1) {
-            if (CT->nnz >= (int64_t)256 * d)
-                hipLaunchKernelGGL(m2_panel2_kernel<true>, dim3(panel_blocks(d, 1, k_tilde)), dim3(kM2Threads), 0, s, *CT,
-                                   T1, k_tilde, 1.0 / n, O, u, M1);
-            else
-                hipLaunchKernelGGL(m2_panel2_kernel<false>, dim3(panel_blocks(d, kPanelRows, k_tilde)), dim3(kM2Threads),
-                                   0, s, *CT, T1, k_tilde, 1.0 / n, O, u, M1);
+            const M2End E{both ? Sp : S, v, O, 1.0 / n, (alpha0 + 1.0) / n, alpha0};
+            const int ldS = both ? pitch : k_tilde;
+            auto second = [&](auto lc, auto uc) {
+                constexpr bool LONG = decltype(lc)::value;
+                hipLaunchKernelGGL((m2_panel2_kernel<LONG, decltype(uc)::value>),
+                                   dim3(panel_blocks(d, LONG ? 1 : kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *CT, T1,
+                                   k_tilde, E, ldS, u, M1);
+            };
+            const bool rows_long = CT->nnz >= (int64_t)256 * d;
+            if (!normalize) rows_long ? second(std::true_type{}, std::true_type{}) : second(std::false_type{}, std::true_type{});
+            else rows_long ? second(std::true_type{}, std::false_type{}) : second(std::false_type{}, std::false_type{});
             if ((st = check_launch("m2_panel2_kernel")) != OTM_OK) return st;
-            hipLaunchKernelGGL(m2_epilogue_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, O, S, u, M1, v,
-                               d, k_tilde, (alpha0 + 1.0) / n, alpha0);
-            if ((st = check_launch("m2_epilogue_kernel")) != OTM_OK) return st;
+            if (normalize) {
+                hipLaunchKernelGGL(m2_epilogue_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, O, S, u, M1,
+                                   v, d, k_tilde, (alpha0 + 1.0) / n, alpha0);
+                if ((st = check_launch("m2_epilogue_kernel")) != OTM_OK) return st;
+            }
         }
         return OTM_OK;
     }

@@ -61,7 +61,8 @@ def test_m2_apply(m, n, d, heavy, normalize):
 
 @pytest.mark.parametrize("n,d,m,per_row,normalize",
                          [(41000, 40500, 50, 6, False), (41000, 40500, 51, 6, True), (42000, 1000, 48, 8, True),
-                          (42000, 40000, 62, 5, True), (64000, 90, 32, 4, True), (20000, 100, 128, 40, False)])
+                          (42000, 40000, 62, 5, True), (64000, 90, 32, 4, True), (20000, 100, 128, 40, False),
+                          (42000, 8000, 48, 5, False)])
 def test_m2_apply_panels(n, d, m, per_row, normalize):
     """Matrices past 16 MB: both passes by panels, the second alone, rows of C^T
     short and long (a workgroup each), m at the ends of a panel with and without room
