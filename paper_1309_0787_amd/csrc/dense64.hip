@@ -37,8 +37,7 @@ namespace {
 // (A = B) is symmetric bit for bit: its tile groups below the diagonal are copies.
 // Before and after, us, with the sum of the parts (FMA on 64 x 64 tiles staged in
 // LDS before): d = 50000, Gram of 200 columns 284 -> 76, A^T B of 200 and Gram
-// of 100 columns together 464 -> 168; d = 10000, Gram of 100 columns 67 -> 23;
-// d = 1000, Gram of 20 columns 47 -> 12.  The matrix cores need 58 us for 50000 x
+// of 100 columns together 464 -> 168; d = 10000, Gram of 100 columns 67 -> 23.  The matrix cores need 58 us for 50000 x
 // 200 x 200 at the 69 TFLOP/s that a large FP64 product reaches, half for a Gram.
 constexpr int kTnT = 4;             // tiles per side of a tile group
 constexpr int kTnMaxParts = 64;
@@ -171,6 +170,74 @@ __global__ void reduce_parts_kernel(const double* __restrict__ part, int nparts,
     out[i] = s;
 }
 
+// The same for few rows: a workgroup per tile of C, its eight waves an eighth of the
+// rows each, 32 rows of loads in flight under the 32 before; the waves' sums meet
+// in LDS, so there are no parts and no second launch.  What bounds both is the
+// loads' latency.  Up to 2048 rows: an orthonormalisation with two Grams, us, by the
+// kernel above and by this one: 20 columns, 500 rows 55.7, 42.8, 1500 rows 57.9, 51.3,
+// 2000 rows 56.7, 55.4, 4000 rows 57.5, 71.8; 200 columns, 250 rows 300, 277, 2000 rows 309,
+// 291, 4000 rows 310, 309.
+constexpr int kTnFewRows = 2048;
+constexpr int kTnFewWaves = 8;
+__global__ __launch_bounds__(64 * kTnFewWaves) void gemm_tn_few_kernel(const double* __restrict__ A, int lda,
+                                                                       const double* __restrict__ B, int ldb, int d,
+                                                                       int p, int q, int tp, int tq, bool gram,
+                                                                       double* __restrict__ C,
+                                                                       const int* __restrict__ run) {
+    if (run != nullptr && *run == 0) return;
+    constexpr int U = 8;
+    __shared__ f64x4 sacc[kTnFewWaves][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int gi = 0, gj = blockIdx.x;
+    if (gram) {
+        while (gj >= tp - gi) gj -= tp - gi++;
+        gj += gi;
+    } else {
+        gi = gj / tq;
+        gj -= gi * tq;
+    }
+    const int per = (d + 4 * kTnFewWaves - 1) / (4 * kTnFewWaves) * 4;
+    const int r0 = min(d, w * per), r1 = min(d, r0 + per);
+    const double* pa = A + min(gi * 16 + l16, p - 1);
+    const double* pb = B + min(gj * 16 + l16, q - 1);
+    double a[2][U], b[2][U];
+    auto load = [&](int s, int r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = r + 4 * u + kq;
+            const size_t at = min(row, d - 1);
+            a[s][u] = pa[at * lda];
+            b[s][u] = pb[at * ldb];
+        }
+    };
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    auto mul = [&](int s, int r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = r + 4 * u + kq < r1;
+            acc = mma64(live ? a[s][u] : 0.0, live ? b[s][u] : 0.0, acc);
+        }
+    };
+    load(0, r0);
+    for (int r = r0; r < r1; r += 8 * U) {
+        load(1, r + 4 * U);
+        mul(0, r);
+        load(0, r + 8 * U);
+        mul(1, r + 4 * U);
+    }
+    sacc[w][lane] = acc;
+    __syncthreads();
+    if (w >= 4) return;
+    double x = sacc[0][lane][w];
+#pragma unroll
+    for (int u = 1; u < kTnFewWaves; ++u) x += sacc[u][lane][w];
+    const int pi = gi * 16 + 4 * w + kq, qj = gj * 16 + l16;
+    if (pi >= p || qj >= q) return;
+    C[(size_t)pi * q + qj] = x;
+    if (gram && gi != gj) C[(size_t)qj * q + pi] = x;
+}
+
 size_t gemm_tn_ws(int d, int p, int q) {
     return ws_round(sizeof(double) * (size_t)tn_shape(d, p, q, p == q).nparts * p * q);
 }
@@ -179,6 +246,11 @@ int gemm_tn(const double* A, int lda, const double* B, int ldb, int d, int p, in
             hipStream_t s, const int* run = nullptr) {
     const bool gram = A == B && lda == ldb && p == q;
     const TnShape t = tn_shape(d, p, q, gram);
+    if (d <= kTnFewRows) {
+        hipLaunchKernelGGL(gemm_tn_few_kernel, dim3(gram ? t.tp * (t.tp + 1) / 2 : t.tp * t.tq), dim3(64 * kTnFewWaves), 0,
+                           s, A, lda, B, ldb, d, p, q, t.tp, t.tq, gram, C, run);
+        return check_launch("gemm_tn_few_kernel");
+    }
     double* out = t.nparts > 1 ? part : C;
     hipLaunchKernelGGL(gemm_tn_kernel, dim3(t.groups, t.nparts), dim3(256), 0, s, A, lda, B, ldb, d, p, q, t, gram, out,
                        run);
