@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,m", [(1, 1), (15, 15), (16, 16), (17, 17), (64, 63), (65, 64), (200, 65), (255, 112),
                                  (257, 113), (259, 128), (1000, 16), (1023, 20), (1500, 129), (2051, 200), (40000, 16),
                                  (33001, 100), (20011, 200), (2048, 33),
-                                 (2049, 33)])
+                                 (2049, 33), (1024, 65), (1025, 65)])
 def test_orthonormalize(d, m):
     g = torch.Generator().manual_seed(d + m)
     Y = torch.randn((d, m), dtype=torch.float64, generator=g)
