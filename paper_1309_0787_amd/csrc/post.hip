@@ -34,8 +34,10 @@ __global__ __launch_bounds__(64) void pi_prep_kernel(const float* __restrict__ P
 // scaled to sum 1, entries below tau cut, scaled again.  A wave owns 16 samples and
 // all k <= 128 rows on the FP64 matrix cores (four consecutive a per lane and block of
 // 16, as the instruction takes any order of the sum), so a sample's row stays in the
-// registers of four lanes and nothing passes through LDS.  k = 100, n = 50000:
-// 110 -> 62 us (FMA from LDS copies, 32 threads of 256 normalizing, before).
+// registers of four lanes and nothing passes through LDS.  The entries are divided by
+// their sum, not multiplied by its reciprocal: one that is tau exactly has to stay (4
+// us).  k = 100, n = 50000: 110 -> 66 us (FMA from LDS copies, 32 threads of 256
+// normalizing, before).
 constexpr int kPiThreads = 256;
 constexpr int kPiSamples = 16 * kPiThreads / 64;
 constexpr int kPiTiles = kMaxK / 16;
@@ -92,27 +94,25 @@ __global__ __launch_bounds__(kPiThreads) void recover_pi_kernel(const TY* __rest
         }
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
-    const double rs = s > 0.0 ? 1.0 / s : 0.0;
 #pragma unroll
     for (int t = 0; t < kPiTiles; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (t >= nt) continue;
-            double v = (s > 0.0) ? acc[t][r] * rs : 0.0;
+            double v = (s > 0.0) ? acc[t][r] / s : 0.0;
             if (v < tau) v = 0.0;
             acc[t][r] = v;
             s2 += v;
         }
     s2 += __shfl_xor(s2, 16);
     s2 += __shfl_xor(s2, 32);
-    const double rs2 = s2 > 0.0 ? 1.0 / s2 : 0.0;
     if (x >= n) return;
 #pragma unroll
     for (int t = 0; t < kPiTiles; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = 16 * t + 4 * r + kq;
-            if (t < nt && i < k) Pi[(size_t)i * n + x] = static_cast<float>((s2 > 0.0) ? acc[t][r] * rs2 : 0.0);
+            if (t < nt && i < k) Pi[(size_t)i * n + x] = static_cast<float>((s2 > 0.0) ? acc[t][r] / s2 : 0.0);
         }
 }
 

@@ -61,3 +61,14 @@ def test_recover_pi(k, n, dtype):
     s = x.sum(0)
     x = np.where(s > 0, x / np.where(s > 0, s, 1), 0)
     assert np.abs(Pi - x)[:, ~near.any(0)].max(initial=0.0) < 1e-6
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8, 64])
+def test_recover_pi_on_the_cut(k):
+    """Entries that are exactly tau stay: k equal positive products have the quotient
+    1 / k, exact in float64 for a k that is a power of two, whatever their size."""
+    y = torch.arange(1, 200, dtype=torch.float32)
+    Y = torch.zeros((y.numel(), otm.default_ldy(k)))
+    Y[:, :k] = y[:, None]
+    Pi = otm.recover_pi(Y.to(dev()), k, torch.eye(k, device=dev()), tau=1.0 / k)
+    assert np.array_equal(Pi.cpu().numpy(), np.full((k, y.numel()), 1.0 / k, dtype=np.float32))
