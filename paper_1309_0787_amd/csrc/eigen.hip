@@ -426,8 +426,8 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
     for (int i = tid; i < n; i += kStatThreads) {
         const double v = sl[i];
         int rank = 0;
-        for (int j = 0; j < n; ++j) rank += sl[j] > v || (sl[j] == v && j < i);
-        if (rank < n) order[rank] = i;
+        for (int j = 0; j < n; ++j) rank += ranks_before(sl[j], j, v, i);
+        order[rank] = i;
     }
 }
 

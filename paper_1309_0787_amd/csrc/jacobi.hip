@@ -193,10 +193,7 @@ __global__ __launch_bounds__(THREADS) void jacobi_lds_kernel(const double* __res
     for (int i = tid; i < n; i += THREADS) {
         const double v = evals[i];
         int rank = 0;
-        for (int j = 0; j < n; ++j) {
-            const double u = evals[j];
-            if (u > v || (u == v && j < i)) ++rank;
-        }
+        for (int j = 0; j < n; ++j) rank += ranks_before(evals[j], j, v, i);
         order[rank] = i;
     }
 }
@@ -352,10 +349,7 @@ __global__ __launch_bounds__(kJacThreads) void jacobi_global_kernel(double* __re
     for (int i = tid; i < n; i += kJacThreads) {
         const double v = evals[i];
         int rank = 0;
-        for (int j = 0; j < n; ++j) {
-            const double u = evals[j];
-            if (u > v || (u == v && j < i)) ++rank;
-        }
+        for (int j = 0; j < n; ++j) rank += ranks_before(evals[j], j, v, i);
         order[rank] = i;
     }
 }

@@ -93,6 +93,13 @@ __device__ __forceinline__ f64x4 mma64(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Value u at position j ranks before v at position i in descending order: ties by
+// position, NaN after every number.  A total order, so ranks are a permutation whatever
+// the values, and a list made from them is whole.
+__device__ __forceinline__ bool ranks_before(double u, int j, double v, int i) {
+    return u > v || (u == v && j < i) || (v != v && (u == u || j < i));
+}
+
 // Entries [b, e) of a CSR row, clamped to [0, nnz]
 __device__ __forceinline__ void clamp_row(const int32_t* rowptr, int64_t nnz, int row, int64_t& b, int64_t& e) {
     b = rowptr[row];
