@@ -5,10 +5,10 @@
 // (Ogita and Aishima, "Iterative refinement for symmetric eigenvalue
 // decomposition", Japan J. Indust. Appl. Math. 35, 2018), which restores
 // eigenvectors and orthogonality to working precision quadratically.  Each step
-// measures its own correction: where the first is below 1e-8 it was the last, since what
-// it leaves is its square; where the second is not either (eigenvalues so close that
-// the twisted factorizations give dependent vectors), *redo is set and the Jacobi
-// solver of jacobi.hip runs instead.
+// measures its own correction: where the first is small enough it was the last, since
+// what it leaves is its square (refine_kernel); where the second is not either
+// (eigenvalues so close that the twisted factorizations give dependent vectors), *redo
+// is set and the Jacobi solver of jacobi.hip runs instead.
 //
 // What bounds it: the reduction is n - 2 dependent steps on one CU (matrix in
 // registers, two barriers a step); everything else is spread over the device but
@@ -378,7 +378,8 @@ __global__ __launch_bounds__(64) void reflect_kernel(const double* __restrict__ 
 }
 
 // Of S = X^T A X and G = X^T X: lam_i = S_ii / G_ii, stat = {threshold under which two
-// eigenvalues count as one, largest |lam|}, order[j] = index of the j-th largest.
+// eigenvalues count as one, the off-diagonal entries that the rotations of jacobi.hip leave},
+// order[j] = index of the j-th largest.
 // (This kernel and the next return at once where run points to 0.)
 constexpr int kStatThreads = 1024;
 __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double* __restrict__ S,
@@ -387,9 +388,9 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
                                                                    int* __restrict__ order, int* __restrict__ flag,
                                                                    const int* __restrict__ run) {
     if (run != nullptr && *run == 0) return;
-    __shared__ double sl[kEigN], red[3][kStatThreads / 64];
+    __shared__ double sl[kEigN], red[4][kStatThreads / 64];
     const int tid = threadIdx.x;
-    double off = 0.0, orth = 0.0, big = 0.0;
+    double off = 0.0, orth = 0.0, big = 0.0, dia = 0.0;
     for (int e = tid; e < n * n; e += kStatThreads) {
         const int i = e / n, j = e - i * n;
         const double s = S[e], g = G[e], r = (i == j ? 1.0 : 0.0) - g;
@@ -400,27 +401,31 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
             sl[i] = s / g;
             lam[i] = sl[i];
             big = fmax(big, fabs(sl[i]));
+            dia += s * s;
         }
     }
     off = wave_sum64(off);
     orth = wave_sum64(orth);
+    dia = wave_sum64(dia);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o));
     if ((tid & 63) == 0) {
         red[0][tid >> 6] = off;
         red[1][tid >> 6] = orth;
         red[2][tid >> 6] = big;
+        red[3][tid >> 6] = dia;
     }
     __syncthreads();
     if (tid == 0) {
-        off = orth = big = 0.0;
+        off = orth = big = dia = 0.0;
         for (int w = 0; w < kStatThreads / 64; ++w) {
             off += red[0][w];
             orth += red[1][w];
             big = fmax(big, red[2][w]);
+            dia += red[3][w];
         }
         stat[0] = 2.0 * (sqrt(off) + big * sqrt(orth));
-        stat[1] = big;
+        stat[1] = 1e-15 * sqrt(dia + off);
         *flag = 0;                                     // for refine_kernel
     }
     for (int i = tid; i < n; i += kStatThreads) {
@@ -431,23 +436,32 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
     }
 }
 
-// E = I + the correction of X; *flag = 1 unless every entry of it is below 1e-8, so
-// that what it leaves is below 1e-16, and the entries between eigenvalues that count
-// as one are rounding errors of S.
+// E = I + the correction C of X.  For the pair (i, j) the residual t = x_i^T (A - lam) x_j
+// has to be symmetric: then C + C^T = I - G whatever the gap of the two eigenvalues,
+// and X (I + C) is orthogonal to second order; an asymmetry of S, a rounding error, would enter
+// it divided by the gap (with S as the two products leave it, eigenvalues 2e-7 apart
+// left 5e-10 of W^T M2 W = I, 2e-15 now).  A pair whose t is down to what the rotations leave
+// and whose angle t / gap is `still` and more all the same (rounding errors over a small
+// gap) is left unrotated, as is one of equal eigenvalues; the first step takes angles
+// whose square the second ends.  *flag = 1 unless every entry of C is below 1e-8 / sqrt(n), so
+// that those of C^2, what the step leaves, are below 1e-16, and the t of every pair not
+// rotated is down to what the rotations leave.
 __global__ __launch_bounds__(256) void refine_kernel(const double* __restrict__ S, const double* __restrict__ G, int n,
                                                      const double* __restrict__ lam, const double* __restrict__ stat,
-                                                     double* __restrict__ E, int* __restrict__ flag,
-                                                     const int* __restrict__ run) {
+                                                     double still, double* __restrict__ E,
+                                                     int* __restrict__ flag, const int* __restrict__ run) {
     if (run != nullptr && *run == 0) return;
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= n * n) return;
     const int i = e / n, j = e - i * n;
-    const double r = (i == j ? 1.0 : 0.0) - G[e], s = S[e];
-    const double gap = lam[j] - lam[i];
-    const bool apart = i != j && fabs(gap) > stat[0];
-    const double c = apart ? (s + lam[j] * r) / gap : 0.5 * r;
+    const double small = 1e-8 / sqrt(static_cast<double>(n));
+    const double r = (i == j ? 1.0 : 0.0) - G[e], s = 0.5 * (S[e] + S[(size_t)j * n + i]);
+    const double gap = lam[j] - lam[i], t = s + 0.5 * (lam[i] + lam[j]) * r;
+    const bool rest = fabs(t) <= stat[1];
+    const bool apart = i != j && fabs(gap) > stat[0] && !(rest && fabs(t) >= still * fabs(gap));
+    const double c = apart ? t / gap + 0.5 * r : 0.5 * r;
     E[e] = (i == j ? 1.0 : 0.0) + c;
-    if (!(fabs(c) < 1e-8) || (!apart && i != j && !(fabs(s) <= 1e-14 * stat[1]))) *flag = 1;
+    if (!(fabs(c) < small) || (!apart && i != j && !rest)) *flag = 1;
 }
 
 // V = U where *run is not 0
@@ -493,8 +507,8 @@ int eigen_direct(const double* A, double* V, int n, double* evals, int* order, i
         hipLaunchKernelGGL(refine_stat_kernel, dim3(1), dim3(kStatThreads), 0, s, S, G, n, evals, stat, order,
                            step == 0 ? more : redo, again);
         if ((st = check_launch("refine_stat_kernel")) != OTM_OK) return st;
-        hipLaunchKernelGGL(refine_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, S, G, n, evals, stat, E,
-                           step == 0 ? more : redo, again);
+        hipLaunchKernelGGL(refine_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, S, G, n, evals, stat,
+                           (step == 0 ? 1e-5 : 1e-8) / std::sqrt(n), E, step == 0 ? more : redo, again);
         if ((st = check_launch("refine_kernel")) != OTM_OK) return st;
         if ((st = gemm_nn_f64(from, n, E, n, to, n, n, n, n, s, again)) != OTM_OK) return st;
     }

@@ -51,3 +51,19 @@ def test_whitener_spectra(kt, kind):
     assert np.abs(ev - ref).max() < 1e-12 * ref[0]
     P = S.T @ W
     assert np.abs(P.T @ M @ P - np.eye(kt)).max() < 1e-9
+
+
+@pytest.mark.parametrize("kt", [33, 64, 65, 100, 200])
+@pytest.mark.parametrize("gap", [1e-4, 1e-5, 1e-6, 2e-7, 1e-8])
+def test_close_eigenvalues_keep_the_precision(kt, gap):
+    """Eigenvectors stay orthogonal to working precision whatever the gaps, so W whitens
+    to it.  Bar: four times n 2^-52, the rounding errors of sums of n terms (the
+    eigenvalues lie within 2% of one another, so nothing enlarges them)."""
+    g = np.random.default_rng(kt)
+    S = np.linalg.qr(g.standard_normal((3 * kt, kt)))[0]
+    V = np.linalg.qr(g.standard_normal((kt, kt)))[0]
+    M = (V * (1.0 + gap * np.arange(kt))) @ V.T
+    M = 0.5 * (M + M.T)
+    W, _, _ = otm.whitener(to_dev(S @ M, torch.float64), to_dev(S, torch.float64), kt, w_lo_dtype=None)
+    P = S.T @ W.cpu().numpy()
+    assert np.abs(P.T @ M @ P - np.eye(kt)).max() < 4 * kt * 2.0**-52
