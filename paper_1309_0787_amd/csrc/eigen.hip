@@ -7,8 +7,13 @@
 // eigenvectors and orthogonality to working precision quadratically.  Each step
 // measures its own correction: where the first is small enough it was the last, since
 // what it leaves is its square (refine_kernel); where the second is not either
-// (eigenvalues so close that the twisted factorizations give dependent vectors), *redo
-// is set and the Jacobi solver of jacobi.hip runs instead.
+// (eigenvalues that differ by rounding errors and a little more, for which the twisted
+// factorizations give dependent vectors), *redo is set and the Jacobi solver of
+// jacobi.hip runs instead.  Eigenvalues that are equal to rounding errors, as those of a
+// matrix of low rank, do not need it: T is cut where it decouples, and within a block
+// they are taken apart first (multisect_kernel).  A whitener of 200 and 100 columns, us, by
+// rotations alone and now: rank 100 7705, 1043; two eigenvalues of 100 each 13500, 802; the
+// identity 702, 635 (with the rotations after the reduction 8520, 14090 and 1690).
 //
 // What bounds it: the reduction is n - 2 dependent steps on one CU (matrix in
 // registers, two barriers a step); everything else is spread over the device but
@@ -95,7 +100,8 @@ __device__ __forceinline__ int tri_slot(int r) { return (r % kTriWaves) * kTriSl
 
 // Elimination of row i (its entries in sm.u, sm.ur); the rows past it are done with.
 __device__ __forceinline__ void tri_step(double (&x)[kTriRows][kTriCols], int i, int n, int w, int lane, TriShared& sm,
-                                         double* __restrict__ e, double* __restrict__ U, double* __restrict__ rh) {
+                                         double tol2, double* __restrict__ e, double* __restrict__ U,
+                                         double* __restrict__ rh) {
     const double* ui = sm.u[i & 1];
     double* uri = sm.ur[i & 1] + w * kTriSlots;
     const int l16 = lane & 15, row16 = lane >> 4;
@@ -107,7 +113,7 @@ __device__ __forceinline__ void tri_step(double (&x)[kTriRows][kTriCols], int i,
     }
     const double alpha = ui[i - 1];
     rest = wave_sum_dpp(rest);
-    if (rest == 0.0) {   // nothing to eliminate (the same in every wave)
+    if (rest <= tol2) {   // nothing to eliminate (the same in every wave)
         if (w == 0 && lane == 0) {
             e[i] = alpha;
             rh[i] = 0.0;
@@ -178,25 +184,33 @@ __device__ __forceinline__ void tri_step(double (&x)[kTriRows][kTriCols], int i,
 // A = Q T Q^T, T tridiagonal (diagonal d, e[i] between i - 1 and i), Q =
 // H_(n-1) ... H_1, H_i = I - U_i U_i^T rh[i] with U_i in row i of U (entries below
 // i).  Rows are eliminated from the last: wave w holds rows w + 8 a, lane l columns
-// l + 64 b of the matrix, in registers.
+// l + 64 b of the matrix, in registers.  A row whose entries to eliminate have a norm
+// within *tol = 1e-15 ||A||_F, what the rotations leave of an entry, is left as it is.
 __global__ __launch_bounds__(kTriThreads) void tridiag_kernel(const double* __restrict__ A, int n,
                                                               double* __restrict__ d, double* __restrict__ e,
                                                               double* __restrict__ U, double* __restrict__ rh,
-                                                              int* __restrict__ redo) {
+                                                              double* __restrict__ tol, int* __restrict__ redo) {
     __shared__ TriShared sm;
+    __shared__ double red[kTriWaves];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double x[kTriRows][kTriCols];
+    double x[kTriRows][kTriCols], part[kTriCols] = {};
 #pragma unroll
     for (int a = 0; a < kTriRows; ++a)
 #pragma unroll
         for (int b = 0; b < kTriCols; ++b) {
             const int r = kTriWaves * a + w, c = lane + 64 * b;
             x[a][b] = (r < n && c < n) ? A[(size_t)r * n + c] : 0.0;
+            part[b] += x[a][b] * x[a][b];
         }
+    double f = wave_sum_dpp((part[0] + part[1]) + (part[2] + part[3]));
+    if (lane == 0) red[w] = f;
     if (threadIdx.x == 0) *redo = 0;
     for (int c = threadIdx.x; c < kTriWaves * kTriSlots; c += kTriThreads) sm.ur[0][c] = sm.ur[1][c] = sm.p[c] = 0.0;
     __syncthreads();
+    f = 0.0;
+    for (int u = 0; u < kTriWaves; ++u) f += red[u];
+    const double small = 1e-15 * sqrt(f), tol2 = small * small;
     for (int i = n - 1; i >= 1; --i) {
         if (w == i % kTriWaves) {
 #pragma unroll
@@ -212,11 +226,12 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_kernel(const double* __re
                     }
         }
         __syncthreads();
-        tri_step(x, i, n, w, lane, sm, e, U, rh);
+        tri_step(x, i, n, w, lane, sm, tol2, e, U, rh);
     }
     if (threadIdx.x == 0) {
         d[0] = x[0][0];
         e[0] = 0.0;
+        *tol = small;
     }
 }
 
@@ -227,33 +242,75 @@ __device__ __forceinline__ double recip(double q) {
     return fma(fma(-q, r, 1.0), r, r);
 }
 
-// lam[m] = the m-th smallest eigenvalue of T, one wave each: 64 Sturm counts at
-// once, so each pass divides the interval by 65.
+// T falls into blocks where |e| is within *tol.  lam[m] = the eigenvalue of row m's
+// block whose place by size is row m's place in it, one wave each: 64 Sturm counts at once, so
+// each pass divides the interval by 65.  blk[m] = the block, first | end << 16.
+//
+// Given `first`, the eigenvalues of a run before, only the blocks with two of them within
+// rounding errors of each other are done again, the diagonal moved by up to 1e-9 of the
+// block's size: eigenvectors of equal eigenvalues are any basis, and the moved
+// ones come out independent, where one eigenvalue would give one vector twice.  The refinement
+// corrects what that changed, to the square of it.  dp = the diagonal used.
 __global__ __launch_bounds__(256) void multisect_kernel(const double* __restrict__ d, const double* __restrict__ e, int n,
-                                                        double* __restrict__ lam) {
-    __shared__ double sd[kEigN], se[kEigN];
+                                                        const double* __restrict__ tol, const double* __restrict__ first,
+                                                        double* __restrict__ lam, double* __restrict__ dp,
+                                                        int* __restrict__ blk) {
+    __shared__ double sdw[4][kEigN], se[kEigN + 1];
     const int lane = threadIdx.x & 63;
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    for (int i = threadIdx.x; i < n; i += 256) {
-        sd[i] = d[i];
-        se[i] = i > 0 ? e[i] * e[i] : 0.0;
-    }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = blockIdx.x * 4 + w;
+    double* sd = sdw[w];
+    const double split = *tol;
+    for (int i = threadIdx.x; i < n; i += 256) se[i] = i > 0 && !(fabs(e[i]) <= split) ? e[i] * e[i] : 0.0;
+    for (int i = lane; i < n; i += 64) sd[i] = d[i];
     __syncthreads();
     if (m >= n) return;
-    double lo = DBL_MAX, hi = -DBL_MAX, emax = 0.0;
-    for (int i = lane; i < n; i += 64) {
-        const double r = sqrt(se[i]) + (i + 1 < n ? sqrt(se[i + 1]) : 0.0);
-        lo = fmin(lo, sd[i] - r);
-        hi = fmax(hi, sd[i] + r);
-        emax = fmax(emax, se[i]);
+    int b0 = 0, b1 = n;
+    for (int c = 0; c < n; c += 64) {
+        const int i = c + lane;
+        const bool cut = i < n && se[i] == 0.0;
+        const uint64_t below = __ballot(cut && i <= m), above = __ballot(cut && i > m);
+        if (below) b0 = c + 63 - __builtin_clzll(below);
+        if (above && b1 == n) b1 = c + __builtin_ctzll(above);
     }
+    double lo, hi, emax;
+    auto bounds = [&]() {
+        lo = DBL_MAX, hi = -DBL_MAX, emax = 0.0;
+        for (int i = b0 + lane; i < b1; i += 64) {
+            const double r = (i > b0 ? sqrt(se[i]) : 0.0) + (i + 1 < b1 ? sqrt(se[i + 1]) : 0.0);
+            lo = fmin(lo, sd[i] - r);
+            hi = fmax(hi, sd[i] + r);
+            if (i > b0) emax = fmax(emax, se[i]);
+        }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, o));
-        hi = fmax(hi, __shfl_xor(hi, o));
-        emax = fmax(emax, __shfl_xor(emax, o));
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+            emax = fmax(emax, __shfl_xor(emax, o));
+        }
+        return fmax(fabs(lo), fabs(hi));
+    };
+    double tn;
+    if (first == nullptr) {
+        tn = bounds();
+        if (lane == 0) blk[m] = b0 | b1 << 16;
+    } else {
+        tn = fmax(fabs(first[b0]), fabs(first[b1 - 1]));
+        bool close = false;
+        for (int i = b0 + 1 + lane; i < b1; i += 64) close = close || first[i] - first[i - 1] <= 1e-13 * tn;
+        if (!__any(close)) {
+            if (lane == 0) {
+                lam[m] = first[m];
+                dp[m] = sd[m];
+            }
+            return;
+        }
+        for (int i = b0 + lane; i < b1; i += 64) sd[i] += 1e-9 * tn * (((uint32_t)i * 2654435761u) * 0x1p-32);
+        __builtin_amdgcn_wave_barrier();               // (sd is this wave's own)
+        tn = bounds();
+        if (lane == 0) dp[m] = sd[m];
     }
-    const double tn = fmax(fabs(lo), fabs(hi)), pivmin = fmax(DBL_MIN * 1e20, emax * 1e-280);
+    const double pivmin = fmax(DBL_MIN * 1e20, emax * 1e-280);
     lo -= 4e-16 * tn;
     hi += 4e-16 * tn;
     for (int pass = 0; pass < 14; ++pass) {
@@ -262,35 +319,49 @@ __global__ __launch_bounds__(256) void multisect_kernel(const double* __restrict
         int cnt = 0;
         double r = 0.0;
 #pragma unroll 8
-        for (int i = 0; i < n; ++i) {
+        for (int i = b0; i < b1; ++i) {
             double q = (sd[i] - x) - se[i] * r;
             if (fabs(q) < pivmin) q = -pivmin;
             cnt += q < 0.0;
             r = __builtin_amdgcn_rcp(q);
             r = fma(fma(-q, r, 1.0), r, r);
         }
-        const uint64_t above = __ballot(cnt > m);      // lanes whose x lies above the eigenvalue
-        const int first = above ? __builtin_ctzll(above) : 64;
-        const double nhi = first < 64 ? __shfl(x, first & 63) : hi, nlo = first > 0 ? __shfl(x, first - 1) : lo;
+        const uint64_t above = __ballot(cnt > m - b0); // lanes whose x lies above the eigenvalue
+        const int at = above ? __builtin_ctzll(above) : 64;
+        const double nhi = at < 64 ? __shfl(x, at & 63) : hi, nlo = at > 0 ? __shfl(x, at - 1) : lo;
         hi = nhi;
         lo = nlo;
     }
     if (lane == 0) lam[m] = 0.5 * (lo + hi);
 }
 
-// Eigenvectors of T to lam, row m of Z for the m-th: T - lam = L D+ L^T from the
-// top and U D- U^T from the bottom, joined at the row where the twisted pivot
-// gamma = D+ + D- - (d - lam) is smallest; a lane per vector, 16 vectors per block.
+// Eigenvectors of T's blocks to lam, row m of Z for the m-th: T - lam = L D+ L^T from the
+// top and U D- U^T from the bottom, joined at the row of the block where the twisted
+// pivot gamma = D+ + D- - (d - lam) is smallest; a lane per vector, 16 vectors per
+// workgroup.  The zeros of e between blocks end the recurrences by themselves.
 constexpr int kTwVec = 16;
 __global__ __launch_bounds__(64) void twisted_kernel(const double* __restrict__ d, const double* __restrict__ e, int n,
-                                                     const double* __restrict__ lam, double* __restrict__ Z) {
+                                                     const double* __restrict__ tol, const double* __restrict__ lam,
+                                                     const int* __restrict__ blk, double* __restrict__ Z) {
     __shared__ double sd[kEigN], se[kEigN], sl[kEigN][kTwVec], su[kEigN][kTwVec], sz[kEigN][kTwVec];
     __shared__ double sn[kTwVec];
     const int t = threadIdx.x, m0 = blockIdx.x * kTwVec;
+    // the rows of this workgroup's blocks
+    const int own = blk[min(m0 + (t & (kTwVec - 1)), n - 1)], b0 = own & 0xffff, b1 = own >> 16;
+    int lo = b0, hi = b1;
+#pragma unroll
+    for (int o = kTwVec / 2; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o));
+        hi = max(hi, __shfl_xor(hi, o));
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+    const int len = hi - lo;
+    const double split = *tol;
     double tn = 0.0;
-    for (int i = t; i < n; i += 64) {
-        sd[i] = d[i];
-        se[i] = e[i];
+    for (int i = t; i < len; i += 64) {
+        sd[i] = d[lo + i];
+        se[i] = fabs(e[lo + i]) <= split ? 0.0 : e[lo + i];
         tn = fmax(tn, fmax(fabs(sd[i]), fabs(se[i])));
     }
 #pragma unroll
@@ -301,22 +372,22 @@ __global__ __launch_bounds__(64) void twisted_kernel(const double* __restrict__ 
         const double la = lam[m0 + t];
         auto safe = [&](double x) { return fabs(x) < tiny ? (x < 0.0 ? -tiny : tiny) : x; };
         double D = safe(sd[0] - la);
-        for (int i = 0; i + 1 < n; ++i) {              // sz: D+
+        for (int i = 0; i + 1 < len; ++i) {            // sz: D+
             sz[i][t] = D;
             const double l = se[i + 1] * recip(D);
             sl[i][t] = l;
             D = safe((sd[i + 1] - la) - se[i + 1] * l);
         }
-        sz[n - 1][t] = D;
-        double best = fabs(D);                         // gamma at the last row is D+
-        int r = n - 1;
-        double M = safe(sd[n - 1] - la);
-        for (int i = n - 1; i >= 1; --i) {
+        sz[len - 1][t] = D;
+        double best = b1 == hi ? fabs(D) : DBL_MAX;    // gamma at the last row is D+
+        int r = b1 - lo - 1;
+        double M = safe(sd[len - 1] - la);
+        for (int i = len - 1; i >= 1; --i) {
             const double u = se[i] * recip(M);
             su[i][t] = u;
             M = safe((sd[i - 1] - la) - se[i] * u);
             const double g = fabs(sz[i - 1][t] + (M - (sd[i - 1] - la)));
-            if (g < best) {
+            if (g < best && i > b0 - lo && i <= b1 - lo) {
                 best = g;
                 r = i - 1;
             }
@@ -329,7 +400,7 @@ __global__ __launch_bounds__(64) void twisted_kernel(const double* __restrict__ 
             nrm += z * z;
         }
         z = 1.0;
-        for (int i = r + 1; i < n; ++i) {
+        for (int i = r + 1; i < len; ++i) {
             z *= -su[i][t];
             sz[i][t] = z;
             nrm += z * z;
@@ -338,7 +409,8 @@ __global__ __launch_bounds__(64) void twisted_kernel(const double* __restrict__ 
     }
     __syncthreads();
     for (int v = 0; v < kTwVec && m0 + v < n; ++v)
-        for (int i = t; i < n; i += 64) Z[(size_t)(m0 + v) * n + i] = sz[i][v] * sn[v];
+        for (int i = t; i < n; i += 64)
+            Z[(size_t)(m0 + v) * n + i] = i >= lo && i < hi ? sz[i - lo][v] * sn[v] : 0.0;
 }
 
 // X[:, m] = H_(n-1) ... H_1 Z[m, :], one wave per vector
@@ -431,8 +503,8 @@ __global__ __launch_bounds__(kStatThreads) void refine_stat_kernel(const double*
     for (int i = tid; i < n; i += kStatThreads) {
         const double v = sl[i];
         int rank = 0;
-        for (int j = 0; j < n; ++j) rank += ranks_before(sl[j], j, v, i);
-        order[rank] = i;
+        for (int j = 0; j < n; ++j) rank += sl[j] > v || (sl[j] == v && j < i);
+        order[rank] = i;                               // (whole unless there is NaN, and then the rotations write it)
     }
 }
 
@@ -476,7 +548,7 @@ __global__ __launch_bounds__(256) void copy_if_kernel(const double* __restrict__
 bool eigen_direct_takes(int n) { return n > 32 && n <= kEigN; }
 
 size_t eigen_direct_ws(int n) {
-    return 6 * ws_round(sizeof(double) * (size_t)n * n) + 5 * ws_round(sizeof(double) * n);
+    return 6 * ws_round(sizeof(double) * (size_t)n * n) + 7 * ws_round(sizeof(double) * n) + ws_round(sizeof(int) * n);
 }
 
 int eigen_direct(const double* A, double* V, int n, double* evals, int* order, int* redo, void* ws, hipStream_t s) {
@@ -485,13 +557,18 @@ int eigen_direct(const double* A, double* V, int n, double* evals, int* order, i
     double *U = wc.take<double>(nn), *Z = wc.take<double>(nn), *X = wc.take<double>(nn), *S = wc.take<double>(nn),
            *G = wc.take<double>(nn), *E = wc.take<double>(nn);
     double *d = wc.take<double>(n), *e = wc.take<double>(n), *rh = wc.take<double>(n), *lam = wc.take<double>(n),
-           *stat = wc.take<double>(n);
+           *stat = wc.take<double>(n), *lam0 = wc.take<double>(n), *dp = wc.take<double>(n);
+    int* blk = wc.take<int>(n);
+    double* tol = stat + 3;
     int st;
-    hipLaunchKernelGGL(tridiag_kernel, dim3(1), dim3(kTriThreads), 0, s, A, n, d, e, U, rh, redo);
+    hipLaunchKernelGGL(tridiag_kernel, dim3(1), dim3(kTriThreads), 0, s, A, n, d, e, U, rh, tol, redo);
     if ((st = check_launch("tridiag_kernel")) != OTM_OK) return st;
-    hipLaunchKernelGGL(multisect_kernel, dim3((n + 3) / 4), dim3(256), 0, s, d, e, n, lam);
-    if ((st = check_launch("multisect_kernel")) != OTM_OK) return st;
-    hipLaunchKernelGGL(twisted_kernel, dim3((n + kTwVec - 1) / kTwVec), dim3(64), 0, s, d, e, n, lam, Z);
+    for (int run = 0; run < 2; ++run) {
+        hipLaunchKernelGGL(multisect_kernel, dim3((n + 3) / 4), dim3(256), 0, s, d, e, n, tol,
+                           run == 0 ? static_cast<const double*>(nullptr) : lam0, run == 0 ? lam0 : lam, dp, blk);
+        if ((st = check_launch("multisect_kernel")) != OTM_OK) return st;
+    }
+    hipLaunchKernelGGL(twisted_kernel, dim3((n + kTwVec - 1) / kTwVec), dim3(64), 0, s, dp, e, n, tol, lam, blk, Z);
     if ((st = check_launch("twisted_kernel")) != OTM_OK) return st;
     hipLaunchKernelGGL(reflect_kernel, dim3(n), dim3(64), 0, s, U, rh, n, Z, X);
     if ((st = check_launch("reflect_kernel")) != OTM_OK) return st;

@@ -67,3 +67,37 @@ def test_close_eigenvalues_keep_the_precision(kt, gap):
     W, _, _ = otm.whitener(to_dev(S @ M, torch.float64), to_dev(S, torch.float64), kt, w_lo_dtype=None)
     P = S.T @ W.cpu().numpy()
     assert np.abs(P.T @ M @ P - np.eye(kt)).max() < 4 * kt * 2.0**-52
+
+
+@pytest.mark.parametrize("kt", [66, 100, 200])
+@pytest.mark.parametrize("kind", ["low rank", "three", "equal", "pairs", "clump", "identity"])
+def test_equal_eigenvalues_take_no_rotations(kt, kind):
+    """Eigenvalues equal to rounding errors are no reason to run the rotations after the
+    direct solver: their log, the largest part of the workspace, stays as it was.  Both
+    eigenproblems of the call (kt columns each, past 64) are the direct solver's."""
+    g = np.random.default_rng(kt)
+    lam = {"low rank": np.where(np.arange(kt) < kt // 2, np.linspace(9.0, 1.0, kt), 0.0),
+           "three": np.where(np.arange(kt) < 3, 3.0 - np.arange(kt), 0.0),
+           "equal": np.repeat([4.0, 1.0], [kt // 2, kt - kt // 2]),
+           "pairs": np.repeat(np.linspace(1.0, 9.0, kt // 2), 2),
+           "clump": np.where(np.arange(kt) < kt // 2, 3.0, np.linspace(1.0, 9.0, kt)),
+           "identity": np.ones(kt)}[kind]
+    V = np.linalg.qr(g.standard_normal((kt, kt)))[0]
+    M = (V * lam) @ V.T
+    M = 0.5 * (M + M.T)
+    S = np.linalg.qr(g.standard_normal((3 * kt, kt)))[0]
+    O, St = to_dev(S @ M, torch.float64), to_dev(S, torch.float64)
+    ws = torch.full((otm.lib().otm_whitener_workspace(3 * kt, kt, kt),), 0xA5, dtype=torch.uint8, device=dev())
+    W = torch.empty((3 * kt, kt), dtype=torch.float64, device=dev())
+    ev = torch.empty(kt, dtype=torch.float64, device=dev())
+    info = torch.zeros(1, dtype=torch.int32, device=dev())
+    otm._check(otm.lib().otm_whitener(O.data_ptr(), St.data_ptr(), 3 * kt, kt, kt, W.data_ptr(), ev.data_ptr(), None,
+                                      otm.F32, kt, info.data_ptr(), ws.data_ptr(), ws.numel(), otm._stream()))
+    assert int(info.item()) == (1 if lam.min() == 0.0 else 0)
+    log_bytes = 60 * (kt - 1) * (kt // 2) * 20               # 60 sweeps of 16-byte rotations and 4-byte pairs
+    untouched = int((ws == 0xA5).sum().item())
+    assert untouched >= log_bytes
+    if lam.min() > 0.0:
+        P = S.T @ W.cpu().numpy()
+        assert np.abs(P.T @ M @ P - np.eye(kt)).max() < 4 * kt * 2.0**-52 * lam.max() / lam.min()
+        assert np.abs(ev.cpu().numpy() - np.sort(lam)[::-1]).max() < 1e-12 * lam.max()
