@@ -963,7 +963,7 @@ extern "C" int otm_whitener(const double* O, const double* S, int32_t d, int32_t
     hipLaunchKernelGGL(symmetrize_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, Gr, k);
     if ((st = check_launch("symmetrize_kernel")) != OTM_OK) return st;
     // (B = O U sigma^(-1/2) has nearly orthogonal columns where S spans an invariant space)
-    if ((st = jacobi(Gr, Vb, k, evb, ordb, jws, s, true)) != OTM_OK) return st;
+    if ((st = jacobi(Gr, Vb, k, evb, ordb, jws, s, Expect::near_diagonal)) != OTM_OK) return st;
     hipLaunchKernelGGL(whiten_scale_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, Vb, evb, ordb, k, info, Pw,
                        evals);
     if ((st = check_launch("whiten_scale_kernel")) != OTM_OK) return st;
@@ -1076,7 +1076,8 @@ extern "C" int otm_unwhiten_topics(const double* W, int32_t d, int32_t k, const 
     if ((st = gemm_tn(W, k, W, k, d, k, k, Gr, part, s)) != OTM_OK) return st;
     hipLaunchKernelGGL(symmetrize_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, Gr, k);
     if ((st = check_launch("symmetrize_kernel")) != OTM_OK) return st;
-    if ((st = jacobi(Gr, V, k, ev, ord, jws, s)) != OTM_OK) return st;
+    // (W from the whitener: its columns are orthogonal to rounding)
+    if ((st = jacobi(Gr, V, k, ev, ord, jws, s, Expect::diagonal)) != OTM_OK) return st;
     hipLaunchKernelGGL(spd_inverse_kernel, dim3((k * k + 255) / 256), dim3(256), 0, s, V, ev, k, Gi, info);
     if ((st = check_launch("spd_inverse_kernel")) != OTM_OK) return st;
     if ((st = gemm_nn(Gi, k, UL, k, Z, k, k, k, k, s)) != OTM_OK) return st;

@@ -2,8 +2,9 @@
 // the projected moment Omega (k_tilde x k_tilde), the Gram of B (k x k) and
 // the Gram of a sketch (m x m), all at most 256 x 256.
 // From 33 to 200 columns the direct solver of eigen.hip takes them, except a
-// near-diagonal matrix of at most 64, which few sweeps solve; these kernels are
-// launched there too and run only where the device flag of that solver says so.
+// near-diagonal matrix of at most 64 and one that is diagonal as a rule, which few
+// sweeps solve; these kernels are launched there too and run only where the device flag
+// of that solver says so.
 //
 // Cyclic two-sided Jacobi in one workgroup.  Rounds follow the round-robin
 // tournament order, so each round applies n/2 disjoint rotations at once:
@@ -367,7 +368,7 @@ size_t jacobi_ws_bytes(int n) {
            (eigen_direct_takes(n) ? eigen_direct_ws(n) : 0);
 }
 
-int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s, bool near_diagonal) {
+int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s, Expect expect) {
     if (n < 1 || n > kJacMaxN) return fail(OTM_ECAPACITY, "eigensolver size must be in [1, 256]");
     if (n <= kJacLdsN) {
         WsCarver wc(ws, jacobi_ws_bytes(n));
@@ -379,8 +380,11 @@ int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hip
         // all of it: 471 us by rotations, 266 with the larger problem direct; kt = 48, k =
         // 24 656, 297; kt = 32 367, even).  A matrix that is nearly diagonal takes few
         // sweeps: there it pays from 65 on (kt = 80, k = 40 444 with the Gram of 40 by
-        // rotations, 572 direct).  The rotations run where the direct solver says so.
-        if (eigen_direct_takes(n) && (!near_diagonal || n > 64)) {
+        // rotations, 572 direct), and for one that is diagonal as a rule never (the Gram of a
+        // whitener's columns in the unwhitening, one sweep: k = 33, d = 500, all of the call
+        // 155 us, 247 direct, k = 128 349, 752).  The rotations run where the direct solver
+        // says so.
+        if (eigen_direct_takes(n) && (expect == Expect::full || (expect == Expect::near_diagonal && n > 64))) {
             redo = wc.take<int>(1);
             int st = eigen_direct(A, V, n, evals, order, redo, wc.take<char>(eigen_direct_ws(n)), s);
             if (st != OTM_OK) return st;

@@ -46,10 +46,11 @@ int validate_csr_header(const otm_csr* C, const char* name);
 // Symmetric FP64 eigensolver for n <= 256 (jacobi.hip): A (n x n, overwritten),
 // V (n x n, eigenvectors as columns), evals[i] = eigenvalue of column i,
 // order[j] = column of the j-th largest eigenvalue.  ws: jacobi_ws_bytes(n).
-// near_diagonal says what to expect of A, for the choice of the method only.
+// expect says what A is like as a rule, for the choice of the method only.
+enum class Expect { full, near_diagonal, diagonal };
 size_t jacobi_ws_bytes(int n);
 int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hipStream_t s,
-           bool near_diagonal = false);
+           Expect expect = Expect::full);
 
 // The same without rotations (eigen.hip), for the n it takes: V, evals, order as
 // above, A kept; *redo = 1 where they are not to working precision.

@@ -101,3 +101,28 @@ def test_equal_eigenvalues_take_no_rotations(kt, kind):
         P = S.T @ W.cpu().numpy()
         assert np.abs(P.T @ M @ P - np.eye(kt)).max() < 4 * kt * 2.0**-52 * lam.max() / lam.min()
         assert np.abs(ev.cpu().numpy() - np.sort(lam)[::-1]).max() < 1e-12 * lam.max()
+
+
+@pytest.mark.parametrize("k", [33, 64, 65, 100, 128])
+def test_unwhitening_takes_rotations(k):
+    """The Gram of a whitener's columns is diagonal to rounding, one sweep of the
+    rotations: their log is written, and nothing of the direct solver's part of the workspace
+    (more than six k x k matrices) beside it."""
+    g = np.random.default_rng(k)
+    W = np.linalg.qr(g.standard_normal((300, k)))[0] * np.linspace(1.0, 9.0, k)
+    Wt, Phi = to_dev(W, torch.float64), torch.eye(k, device=dev())
+    ws = torch.full((otm.lib().otm_unwhiten_workspace(300, k),), 0xA5, dtype=torch.uint8, device=dev())
+    mu = torch.empty((300, k), dtype=torch.float64, device=dev())
+    ah, lam = (torch.empty(k, dtype=torch.float64, device=dev()) for _ in range(2))
+    info = torch.zeros(1, dtype=torch.int32, device=dev())
+    otm._check(otm.lib().otm_unwhiten_topics(Wt.data_ptr(), 300, k, Phi.data_ptr(), 1.0, mu.data_ptr(), ah.data_ptr(),
+                                             lam.data_ptr(), info.data_ptr(), ws.data_ptr(), ws.numel(), otm._stream()))
+    assert int(info.item()) == 0
+    players = (k + 1) // 2 * 2
+    sweep = (players - 1) * (players // 2)
+    written = int((ws != 0xA5).sum().item())
+    # the call's own five matrices and column sums, one sweep of 20-byte rotations
+    assert written <= 8 * (5 * k * k + 131 * k) + 20 * sweep + 4096
+    ref = W @ np.linalg.inv(W.T @ W)
+    ref = np.maximum(ref, 0.0)
+    assert np.abs(mu.cpu().numpy() - ref / ref.sum(0)).max() < 1e-12
