@@ -17,6 +17,7 @@
 //    one workgroup the running minimum of m p_(r) / r from the largest rank
 //    down, capped at 1; edges p_adj <= threshold; recovery ratio and error.
 //  * bridgeness (Eq. bridgeness) and its degree-corrected form.
+#include <algorithm>
 #include <cmath>
 
 #include "otm_internal.h"
@@ -28,7 +29,7 @@ constexpr int kStatThreads = 1024;
 constexpr int kTile = 64;            // rows of each side per workgroup of pair_stats
 constexpr int kPair = 4;             // pairs per thread and side
 constexpr int kChunk = 64;           // nodes staged per LDS round
-constexpr int kNodesPerBlock = 384;  // nodes per split of the pair sums
+constexpr int kMaxNodes = 2048;      // nodes per split of the pair sums, at most
 constexpr int kMaxTests = 16384;     // k_hat * k (128 x 128)
 
 __device__ double block_sum(double v, double* red) {
@@ -75,14 +76,14 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __
 // additions and products alone take 60 at full rate; on the matrix cores the cross
 // sums made it 224).
 __global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict__ Ph, int kh,
-                                                         const float* __restrict__ P, int k, int n,
+                                                         const float* __restrict__ P, int k, int n, int per,
                                                          const double* __restrict__ mean, double* __restrict__ cross,
                                                          double* __restrict__ l1) {
     // node-major; the pitch keeps 16-byte reads aligned
     __shared__ __attribute__((aligned(16))) double sa[kChunk][kTile + 2];
     __shared__ __attribute__((aligned(16))) double sb[kChunk][kTile + 2];
     const int i0 = blockIdx.x * kTile, j0 = blockIdx.y * kTile, z = blockIdx.z;
-    const int x0 = z * kNodesPerBlock, x1 = min(n, x0 + kNodesPerBlock);
+    const int x0 = z * per, x1 = min(n, x0 + per);
     const int ti = threadIdx.x / 16 * kPair, tj = threadIdx.x % 16 * kPair;
     double ma[kPair], mb[kPair], c[kPair][kPair], l[kPair][kPair];
 #pragma unroll
@@ -383,7 +384,22 @@ __global__ void bridgeness_kernel(const float* __restrict__ Ph, int kh, int n, o
     }
 }
 
-int n_splits(int n) { return (n + kNodesPerBlock - 1) / kNodesPerBlock; }
+// Nodes per split of the pair sums: rounds of two workgroups a CU (512) over all tiles
+// of pairs, as few rounds as keep a split within kMaxNodes, which bounds the scratch at large n
+// and n itself (65535 splits).  The whole call, us, with 384 nodes to a split whatever the
+// sizes, and now: one pair, 500 nodes 90, 48; 17 x 17, 5000 175, 140; 100 x 100, 50000 258,
+// 233; 65 x 65, 400000 1155, 1239 (tiles of one row and column end early there, and a
+// round of even splits waits for the others).
+int split_nodes(int k_hat, int k, int n) {
+    const int64_t tiles = (int64_t)((k_hat + kTile - 1) / kTile) * ((k + kTile - 1) / kTile);
+    const int64_t most = (int64_t)512 * kMaxNodes, rounds = (n * tiles + most - 1) / most;
+    const int64_t per = (n * tiles + 512 * rounds - 1) / (512 * rounds);
+    return static_cast<int>(std::max<int64_t>(kChunk, (per + 7) / 8 * 8));
+}
+int n_splits(int k_hat, int k, int n) {
+    const int per = split_nodes(k_hat, k, n);
+    return (int)(((int64_t)n + per - 1) / per);
+}
 
 }  // namespace
 }  // namespace otm
@@ -394,7 +410,7 @@ extern "C" size_t otm_validate_workspace(int32_t k_hat, int32_t k, int32_t n) {
     if (k_hat < 1 || k < 1 || n < 3) return 0;
     const size_t m = (size_t)k_hat * k;
     size_t b = ws_round(sizeof(double) * (k_hat + k)) * 2;            // means, sums of squares
-    b += ws_round(sizeof(double) * m * n_splits(n)) * 2;              // partial cross and l1 sums
+    b += ws_round(sizeof(double) * m * n_splits(k_hat, k, n)) * 2;              // partial cross and l1 sums
     b += ws_round(sizeof(int) * m);                                   // ranks
     return b;
 }
@@ -411,7 +427,7 @@ extern "C" int otm_validate(const float* Pi_hat, int32_t k_hat, const float* Pi,
     OTM_REQUIRE(ws && ws_bytes >= otm_validate_workspace(k_hat, k, n), OTM_EWORKSPACE, "validate workspace too small");
     hipStream_t s = as_stream(stream);
     WsCarver wc(ws, ws_bytes);
-    const int m = k_hat * k, nz = n_splits(n);
+    const int m = k_hat * k, nz = n_splits(k_hat, k, n);
     double* mean = wc.take<double>(k_hat + k);
     double* ss = wc.take<double>(k_hat + k);
     double* cross = wc.take<double>((size_t)m * nz);
@@ -421,7 +437,8 @@ extern "C" int otm_validate(const float* Pi_hat, int32_t k_hat, const float* Pi,
     hipLaunchKernelGGL(row_stats_kernel, dim3(k_hat + k), dim3(kStatThreads), 0, s, Pi_hat, k_hat, Pi, n, mean, ss);
     if ((st = check_launch("row_stats_kernel")) != OTM_OK) return st;
     dim3 grid((k_hat + kTile - 1) / kTile, (k + kTile - 1) / kTile, nz);
-    hipLaunchKernelGGL(pair_stats_kernel, grid, dim3(256), 0, s, Pi_hat, k_hat, Pi, k, n, mean, cross, l1p);
+    hipLaunchKernelGGL(pair_stats_kernel, grid, dim3(256), 0, s, Pi_hat, k_hat, Pi, k, n,
+                       split_nodes(k_hat, k, n), mean, cross, l1p);
     if ((st = check_launch("pair_stats_kernel")) != OTM_OK) return st;
     hipLaunchKernelGGL(finalize_kernel, dim3((m + 63) / 64), dim3(64 * kFinParts), 0, s, cross, l1p, nz, k_hat, k, n,
                        ss, rho, pval, l1, rank);

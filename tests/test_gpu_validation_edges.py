@@ -72,3 +72,18 @@ def test_recover_pi_on_the_cut(k):
     Y[:, :k] = y[:, None]
     Pi = otm.recover_pi(Y.to(dev()), k, torch.eye(k, device=dev()), tau=1.0 / k)
     assert np.array_equal(Pi.cpu().numpy(), np.full((k, y.numel()), 1.0 / k, dtype=np.float32))
+
+
+@pytest.mark.parametrize("kh,k,n", [(5, 5, 32767), (5, 5, 32769), (3, 2, 1_048_575), (3, 2, 1_050_000), (70, 3, 524_289)])
+def test_validate_ranges(kh, k, n):
+    """Node ranges of one chunk and of two, and of 2048 nodes with a short last one
+    (bar as above, times 30 for sums of 1e6 terms: rounding errors add up like their root)."""
+    g = np.random.default_rng(n)
+    A, B = g.random((kh, n)).astype(np.float32), g.random((k, n)).astype(np.float32)
+    v = otm.validate(to_dev(A), to_dev(B), threshold=0.05)
+    a, b = A.astype(np.float64), B.astype(np.float64)
+    ac, bc = a - a.mean(1, keepdims=True), b - b.mean(1, keepdims=True)
+    rho = ac @ bc.T / np.sqrt((ac**2).sum(1))[:, None] / np.sqrt((bc**2).sum(1))[None]
+    assert np.abs(v.rho.cpu().numpy() - rho).max() < 3e-11
+    l1 = np.stack([np.abs(a[i] - b).mean(1) for i in range(kh)])
+    assert rel(v.l1.cpu().numpy(), l1) < 3e-11
