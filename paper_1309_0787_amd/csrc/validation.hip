@@ -264,9 +264,10 @@ __global__ __launch_bounds__(kRankThreads) void rank_kernel(const double* __rest
 #pragma unroll 16
         for (int t = 0; t < cnt; ++t) r += sp[t] < pe ? 1 : 0;
     } else {
+#pragma unroll 16
         for (int t = 0; t < cnt; ++t) {
             const double q = sp[t];
-            r += (q < pe || (q == pe && f0 + t < e)) ? 1 : 0;
+            r += (q < pe ? 1 : 0) + (q == pe && f0 + t < e ? 1 : 0);
         }
     }
     if (e < m && r > 0) atomicAdd(&rank[e], r);
