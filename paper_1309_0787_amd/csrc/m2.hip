@@ -75,6 +75,7 @@ template <bool V2, int NU, class F>
 __device__ __forceinline__ void m2_gather(const otm_csr& A, int64_t b, int64_t e, const double* __restrict__ X, int m,
                                           int lane, double (&acc)[NU], F&& entry) {
     constexpr int U = NU == 2 ? 8 : 4;   // rows in flight
+    if (A.n_cols < 1) return;            // (X has no row to read in place of a bad one)
     for (int64_t base = b; base < e; base += 64) {
         const int cnt = e - base < 64 ? static_cast<int>(e - base) : 64;
         int32_t c = -1;

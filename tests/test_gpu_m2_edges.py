@@ -87,3 +87,40 @@ def test_m2_apply_panels(n, d, m, per_row, normalize):
     torch.cuda.synchronize()
     assert rel(O.cpu().numpy(), ref) < 1e-12
     assert torch.equal(O, again)
+
+
+@pytest.mark.parametrize("m", [7, 40, 128, 130, 200])
+def test_columns_out_of_range_are_skipped(m):
+    """Entries with a column outside the matrix count for nothing, in short rows and long ones,
+    by rows and by panels; a matrix without columns leaves nothing of X to read."""
+    g = np.random.default_rng(m)
+    n, d = 60000 if m >= 40 else 700, 300
+    per = 12
+    cols = g.integers(0, d, (n, per)).astype(np.int64)
+    bad = g.random((n, per)) < 0.2
+    ci = np.where(bad, np.where(g.random((n, per)) < 0.5, -1 - cols, d + cols), cols).astype(np.int32)
+    rp = np.arange(0, n * per + 1, per, dtype=np.int32)
+    A = _dev_csr(rp, ci.reshape(-1), np.ones(n * per, np.float32), d)
+    # its transpose, with bad columns put among the good ones of every row
+    r, c = np.repeat(np.arange(n), per)[~bad.reshape(-1)], cols.reshape(-1)[~bad.reshape(-1)]
+    extra = int(bad.sum())
+    rows = np.concatenate([c, g.integers(0, d, extra)])
+    cc = np.concatenate([r, np.where(g.random(extra) < 0.5, -7, n + 3)])
+    o = np.argsort(rows, kind="stable")
+    rpt = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=d))]).astype(np.int32)
+    AT = _dev_csr(rpt, cc[o].astype(np.int32), np.ones(n * per, np.float32), n)
+    S = g.standard_normal((d, m))
+    C = np.zeros((n, d))
+    np.add.at(C, (r, c), 1.0)
+    M1 = C.sum(0) / n
+    ref = 1.7 / n * (C.T @ (C @ S) - C.sum(0)[:, None] * S) - 0.7 * np.outer(M1, M1 @ S)
+    O = otm.m2_apply(A, AT, False, 0.7, torch.from_numpy(S).to(dev()))
+    assert rel(O.cpu().numpy(), ref) < 1e-12
+    # Pairs V = (1/n) G1T (G2 V) with G2 of no columns
+    E = otm.DeviceCSR(n, 0, A.rowptr, A.colidx, None).c()
+    G = AT.c()
+    V = torch.ones(8, dtype=torch.float64, device=dev())
+    out = torch.full((d, m), 5.0, dtype=torch.float64, device=dev())
+    ws = torch.empty(otm.lib().otm_pairs_apply_workspace(n, m), dtype=torch.uint8, device=dev())
+    otm._check(otm.lib().otm_pairs_apply(G, E, V.data_ptr(), m, out.data_ptr(), ws.data_ptr(), ws.numel(), otm._stream()))
+    assert torch.equal(out, torch.zeros_like(out))
