@@ -542,11 +542,14 @@ int m2_blocks(int64_t waves) {
 // m = 200 1649, 1016; m = 40 338, 306; 20000 x 20000, nnz = 1.2e6, m = 100 231, 185, m = 64
 // 131, 137; 10000 x 10000, m = 120 99, 114; documents, d = 10000, nnz = 6e6, n = 40000,
 // m = 100 967, 628), and where a panel of 16 columns is not mostly padding.
-bool panels_fit(int rows, int m) { return m >= 32 && (int64_t)rows * m >= 2000000; }
+bool panels_fit(int rows, int m) {
+    // (a launch holds fewer than 2^32 threads, and the padding takes one per value)
+    return m >= 32 && (int64_t)rows * m >= 2000000 && (int64_t)rows * panel_count(m) * kPanel < (int64_t(1) << 32);
+}
 
-unsigned panel_blocks(int rows, int per, int m) {
+int64_t panel_blocks(int rows, int per, int m) {
     const int64_t total = (int64_t)((rows + per - 1) / per) * panel_count(m);
-    return static_cast<unsigned>(kXcds * ((total + kXcds - 1) / kXcds));
+    return kXcds * ((total + kXcds - 1) / kXcds);
 }
 
 // Shares of m2_split_kernel at most: enough to fill the device eight times over
@@ -753,7 +756,7 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
             hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, s, S, padded,
                                k_tilde, pitch, Sp);
             if ((st = check_launch("pad_rows_kernel")) != OTM_OK) return st;
-            hipLaunchKernelGGL(m2_panel1_kernel, dim3(panel_blocks(n, kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *C,
+            hipLaunchKernelGGL(m2_panel1_kernel, dim3((unsigned)panel_blocks(n, kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *C,
                                normalize, Sp, k_tilde, T1, vpart, info);
         } else {
             nb = m2_blocks(n);
@@ -771,10 +774,11 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
             auto second = [&](auto lc, auto uc) {
                 constexpr bool LONG = decltype(lc)::value;
                 hipLaunchKernelGGL((m2_panel2_kernel<LONG, decltype(uc)::value>),
-                                   dim3(panel_blocks(d, LONG ? 1 : kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *CT, T1,
+                                   dim3((unsigned)panel_blocks(d, LONG ? 1 : kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *CT, T1,
                                    k_tilde, E, ldS, u, M1);
             };
-            const bool rows_long = CT->nnz >= (int64_t)256 * d;
+            // (a workgroup to each row and panel, where a launch holds as many)
+            const bool rows_long = CT->nnz >= (int64_t)256 * d && panel_blocks(d, 1, k_tilde) * kM2Threads < (int64_t(1) << 32);
             if (!normalize) rows_long ? second(std::true_type{}, std::true_type{}) : second(std::false_type{}, std::true_type{});
             else rows_long ? second(std::true_type{}, std::false_type{}) : second(std::false_type{}, std::false_type{});
             if ((st = check_launch("m2_panel2_kernel")) != OTM_OK) return st;

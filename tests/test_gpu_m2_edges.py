@@ -124,3 +124,24 @@ def test_columns_out_of_range_are_skipped(m):
     ws = torch.empty(otm.lib().otm_pairs_apply_workspace(n, m), dtype=torch.uint8, device=dev())
     otm._check(otm.lib().otm_pairs_apply(G, E, V.data_ptr(), m, out.data_ptr(), ws.data_ptr(), ws.numel(), otm._stream()))
     assert torch.equal(out, torch.zeros_like(out))
+
+
+def test_many_long_rows():
+    """A million rows of C^T of 256 entries, 256 columns: a workgroup to each row and
+    panel would be more threads than a launch holds.  The matrix is circulant, so rows of
+    the result follow from 256 x 256 rows of S; entries agree within 1e-12 of the row's largest
+    (sums of 65536 terms)."""
+    d = m = 256
+    n = 1_000_000
+    o = torch.from_numpy(np.random.default_rng(0).permutation(n)[:d].astype(np.int32)).to(dev())
+    t = torch.arange(n, dtype=torch.int32, device=dev())
+    rp = torch.arange(0, n * d + 1, d, dtype=torch.int32, device=dev())
+    A = otm.DeviceCSR(n, n, rp, ((t[:, None] + o) % n).reshape(-1))
+    AT = otm.DeviceCSR(n, n, rp, ((t[:, None] - o + n) % n).reshape(-1))
+    S = torch.randn((n, m), dtype=torch.float64, device=dev(), generator=torch.Generator(device=dev()).manual_seed(1))
+    O = otm.m2_apply(A, AT, False, 0.7, S)
+    v = d * S.sum(0) / n
+    for a in (0, 1, 63, 64, 500_001, n - 1):
+        rows = (a - o[:, None].long() + o[None].long()) % n
+        ref = 1.7 / n * (S[rows.reshape(-1)].sum(0) - d * S[a]) - 0.7 * d / n * v
+        assert (O[a] - ref).abs().max() <= 1e-12 * ref.abs().max(), a
