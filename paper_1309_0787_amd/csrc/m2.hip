@@ -20,7 +20,6 @@
 //
 // Malformed CSR cannot make these kernels read out of bounds: row ranges are
 // clamped to [0, nnz] and entries with a column outside [0, n_cols) are skipped.
-#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -552,8 +551,18 @@ int64_t panel_blocks(int rows, int per, int m) {
     return kXcds * ((total + kXcds - 1) / kXcds);
 }
 
-// Shares of m2_split_kernel at most: enough to fill the device eight times over
-int m2_shares(int d) { return static_cast<int>(16 * (int64_t)d < 65536 ? 16 * (int64_t)d : 65536); }
+// Workgroups of the first pass, each with its part of v
+size_t m2_vparts(int n, int d, int m) {
+    if (panels_fit(n, m) && panels_fit(d, m)) return ((size_t)n + kPanelRows - 1) / kPanelRows;
+    return m2_blocks(n);
+}
+
+// Shares of m2_split_kernel at most: enough to fill the device (32 waves a CU).  Room for
+// their sums, which the workspace has whether the rows turn out long or not, is what
+// stands against more: 65536 shares, eight times the room, take the whole call (20000
+// documents of 10000 words, nnz = 4e6, m = 20) from 231 us to 224, but 300000 of 2000,
+// nnz = 1e7, from 778 to 861.
+int m2_shares(int d) { return static_cast<int>(16 * (int64_t)d < 8192 ? 16 * (int64_t)d : 8192); }
 
 __global__ void set_i32_kernel(int32_t* __restrict__ out, int32_t v) { *out = v; }
 
@@ -703,21 +712,17 @@ using namespace otm;
 
 extern "C" size_t otm_m2_apply_workspace(int32_t n, int32_t d, int32_t k_tilde) {
     if (n < 0 || d < 0 || k_tilde < 1) return 0;
-    size_t b = 0;
-    b += ws_round(sizeof(double) * (size_t)n * k_tilde);  // T1
-    b += 2 * ws_round(sizeof(double) * (size_t)n);        // w1, w2
-    b += ws_round(sizeof(double) * (size_t)kM2MaxBlocks * k_tilde);
-    b += ws_round(sizeof(double) * (size_t)k_tilde);      // v
-    b += ws_round(sizeof(double) * (size_t)2 * m2_shares(d) * (k_tilde + 2));
-    if (panels_fit(n, k_tilde)) {                         // padded T1 and S, w1, w2, u, M1, v and its parts
+    const size_t m = k_tilde;
+    size_t b = 2 * ws_round(sizeof(double) * (size_t)n) + ws_round(sizeof(double) * m);   // w1, w2, v
+    if (panels_fit(n, k_tilde)) {                         // padded T1 and S, u, M1, v's parts
         const size_t pitch = (size_t)panel_count(k_tilde) * kPanel;
-        size_t p = ws_round(sizeof(double) * pitch * n) + ws_round(sizeof(double) * pitch * d);
-        p += 2 * ws_round(sizeof(double) * (size_t)n) + 2 * ws_round(sizeof(double) * (size_t)d);
-        p += ws_round(sizeof(double) * (size_t)k_tilde);
-        p += ws_round(sizeof(double) * pitch * std::max((size_t)n / kPanelRows + 1, (size_t)kM2MaxBlocks));
-        b = b > p ? b : p;
+        b += ws_round(sizeof(double) * pitch * n) + 2 * ws_round(sizeof(double) * (size_t)d);
+        if (panels_fit(d, k_tilde)) b += ws_round(sizeof(double) * pitch * d);
+        return b + ws_round(sizeof(double) * m2_vparts(n, d, k_tilde) * pitch);
     }
-    return b;
+    b += ws_round(sizeof(double) * (size_t)n * m);        // T1, v's parts, the shares' sums
+    b += ws_round(sizeof(double) * m2_vparts(n, d, k_tilde) * m);
+    return b + ws_round(sizeof(double) * (size_t)2 * m2_shares(d) * (m + 2));
 }
 
 extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, double alpha0, const double* S,
@@ -739,18 +744,18 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
     WsCarver wc(ws, ws_bytes);
     if (panels_fit(n, k_tilde)) {
         const int pitch = panel_count(k_tilde) * kPanel;
+        const bool both = panels_fit(d, k_tilde);
         double* T1 = wc.take<double>((size_t)pitch * n);
-        double* Sp = wc.take<double>((size_t)pitch * d);
+        double* Sp = wc.take<double>(both ? (size_t)pitch * d : 0);
         double* w1 = wc.take<double>(n);
         double* w2 = wc.take<double>(n);
         double* u = wc.take<double>(d);
         double* M1 = wc.take<double>(d);
         double* v = wc.take<double>(k_tilde);
-        int nb = (n + kPanelRows - 1) / kPanelRows;
-        double* vpart = wc.take<double>((size_t)pitch * std::max(nb, kM2MaxBlocks));
+        const int nb = static_cast<int>(m2_vparts(n, d, k_tilde));
+        double* vpart = wc.take<double>((size_t)pitch * nb);
         hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, s, info, 0);
         if ((st = check_launch("set_i32_kernel")) != OTM_OK) return st;
-        const bool both = panels_fit(d, k_tilde);
         const int64_t padded = (int64_t)pitch * d, total = (int64_t)d * k_tilde;
         if (both) {
             hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, s, S, padded,
@@ -759,7 +764,6 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
             hipLaunchKernelGGL(m2_panel1_kernel, dim3((unsigned)panel_blocks(n, kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *C,
                                normalize, Sp, k_tilde, T1, vpart, info);
         } else {
-            nb = m2_blocks(n);
             m2_dispatch(k_tilde, reinterpret_cast<uintptr_t>(S) % 16 == 0, [&](auto v2c, auto nuc) {
                 hipLaunchKernelGGL((m2_pass1_kernel<v2c.value, nuc.value>), dim3(nb), dim3(kM2Threads), 0, s, *C,
                                    normalize, S, k_tilde, pitch, T1, w1, w2, vpart, info);
@@ -793,12 +797,12 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
     double* T1 = wc.take<double>((size_t)n * k_tilde);
     double* w1 = wc.take<double>(n);
     double* w2 = wc.take<double>(n);
-    double* vpart = wc.take<double>((size_t)kM2MaxBlocks * k_tilde);
+    const int b1 = static_cast<int>(m2_vparts(n, d, k_tilde));
+    double* vpart = wc.take<double>((size_t)b1 * k_tilde);
     double* v = wc.take<double>(k_tilde);
     double* part = wc.take<double>((size_t)2 * m2_shares(d) * (k_tilde + 2));
     hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, s, info, 0);
     if ((st = check_launch("set_i32_kernel")) != OTM_OK) return st;
-    const int b1 = m2_blocks(n);
     const M2End E{S, v, O, 1.0 / n, (alpha0 + 1.0) / n, alpha0};
     // Rows of C^T of 256 entries and more (documents: a word occurs in thousands
     // of them) are too few to fill the device evenly, and their lengths differ by

@@ -145,3 +145,30 @@ def test_many_long_rows():
         rows = (a - o[:, None].long() + o[None].long()) % n
         ref = 1.7 / n * (S[rows.reshape(-1)].sum(0) - d * S[a]) - 0.7 * d / n * v
         assert (O[a] - ref).abs().max() <= 1e-12 * ref.abs().max(), a
+
+
+@pytest.mark.parametrize("n,d,m,per", [(300, 200, 40, 5), (20000, 70, 20, 40), (3000, 9, 256, 6), (42000, 41000, 50, 4),
+                                       (64000, 90, 32, 6), (42000, 41000, 49, 5)])
+def test_workspace_is_all_that_is_written(n, d, m, per):
+    """The layout of every path stays inside the size that the workspace function gives: bytes past
+    it keep their value, and the result is that of a roomier one."""
+    g = np.random.default_rng(n + m)
+    key = np.unique(g.integers(0, n, n * per).astype(np.int64) * d + g.integers(0, d, n * per))
+    r, c = key // d, key % d
+    rp = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int32)
+    o = np.argsort(c, kind="stable")
+    rpt = np.concatenate([[0], np.cumsum(np.bincount(c, minlength=d))]).astype(np.int32)
+    one = np.ones(len(r), np.float32)
+    A, AT = _dev_csr(rp, c.astype(np.int32), one, d), _dev_csr(rpt, r[o].astype(np.int32), one, n)
+    S = torch.from_numpy(g.standard_normal((d, m))).to(dev())
+    size, guard = otm.lib().otm_m2_apply_workspace(n, d, m), 1 << 20
+    ws = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device=dev())
+    O = torch.empty((d, m), dtype=torch.float64, device=dev())
+    info = torch.zeros(1, dtype=torch.int32, device=dev())
+    otm._check(otm.lib().otm_m2_apply(A.c(), AT.c(), 0, 0.7, S.data_ptr(), m, O.data_ptr(), info.data_ptr(),
+                                      ws.data_ptr(), size, otm._stream()))
+    kept = int((ws[size:] == 0xA5).sum().item())
+    assert kept == guard
+    assert torch.equal(O, otm.m2_apply(A, AT, False, 0.7, S))
+    assert otm.lib().otm_m2_apply(A.c(), AT.c(), 0, 0.7, S.data_ptr(), m, O.data_ptr(), info.data_ptr(),
+                                  ws.data_ptr(), size - 1, otm._stream()) == -7
