@@ -517,6 +517,64 @@ __global__ __launch_bounds__(kM2Threads) void spmm64_kernel(otm_csr C, const dou
     }
 }
 
+// The same for an X past L2, four entries at a time, their indices loaded by every lane.
+// The columns of a row ascend, so waves that go at one pace gather from one part of X
+// and find it in L2; waves with 64 indices at hand run apart, and that part grows past L2
+// (10000 x 10000, nnz = 1e6, m = 200: of 13.5 million lines 8.1 million missed in L2,
+// 4.8 by this loop).  What slows it is what keeps the pace: with the indices by scalar loads
+// it takes as long as the other (298 us, 203; the other 294).
+template <bool V2>
+__global__ __launch_bounds__(kM2Threads) void spmm64_paced_kernel(otm_csr C, const double* __restrict__ X, int m,
+                                                                  double scale, double* __restrict__ Y) {
+    constexpr int U = 4, NU = 4;
+    const int lane = threadIdx.x & 63;
+    const int wave = (blockIdx.x * kM2Threads + threadIdx.x) >> 6;   // (not m2_wave: the indices by vector loads)
+    const int nwaves = gridDim.x * kM2Waves;
+    for (int row = wave; row < C.n_rows; row += nwaves) {
+        int64_t b, e;
+        clamp_row(C.rowptr, C.nnz, row, b, e);
+        double acc[NU] = {};
+        auto entries = [&](int64_t p, auto count) {
+            constexpr int N = decltype(count)::value;
+            int32_t c[N];
+            double v[N], x[N][NU];
+#pragma unroll
+            for (int y = 0; y < N; ++y) {
+                c[y] = C.colidx[p + y];
+                v[y] = C.vals ? static_cast<double>(C.vals[p + y]) : 1.0;
+                if (c[y] < 0 || c[y] >= C.n_cols) c[y] = -1;
+            }
+#pragma unroll
+            for (int y = 0; y < N; ++y) m2_load<V2, NU>(X + (size_t)(c[y] < 0 ? 0 : c[y]) * m, lane, m, x[y]);
+#pragma unroll
+            for (int y = 0; y < N; ++y) {
+                if (c[y] < 0) continue;
+#pragma unroll
+                for (int u = 0; u < NU; ++u) acc[u] += v[y] * x[y][u];
+            }
+        };
+        int64_t p = b;
+        for (; p + U <= e; p += U) entries(p, std::integral_constant<int, U>{});
+        for (; p < e; ++p) entries(p, std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int col = m2_col<V2>(lane, u);
+            if (col < m) Y[(size_t)row * m + col] = scale * acc[u];
+        }
+    }
+}
+
+// Where that loop is the faster one: X past 10 MB in rows of more than 128 doubles, past 20 MB
+// in rows of 100 and more, and rows of C long enough to keep a pace.  Two products in
+// turn, us, the other loop and this: 10000 x 10000, nnz = 1e6, m = 160 214, 182, m = 200
+// 294, 203 (m = 128 150, 163); 5000 x 5000, nnz = 5e5, m = 256 118, 103 (m = 200 87, 102);
+// 20000 x 20000, nnz = 2e6, m = 128 426, 342 (m = 100 332, 342); 30000 x 30000, nnz = 3e6, m = 100
+// 583, 521; (50000 x 50000, nnz = 1e6, m = 200 465, 471).
+bool paced(const otm_csr& C, int m) {
+    const int64_t bytes = (int64_t)sizeof(double) * C.n_cols * m;
+    return (m > 128 ? bytes >= 10000000 : m >= 100 && bytes >= 20000000) && C.nnz >= (int64_t)32 * C.n_rows;
+}
+
 // Rows of up to 128 doubles take two columns per lane, wider ones four; 16-byte
 // loads where every row begins 16-byte aligned.
 template <class F>
@@ -700,8 +758,12 @@ int spmm64(const otm_csr& C, const double* X, int m, double scale, double* Y, hi
     if (m < 1 || m > 256) return fail(OTM_ECAPACITY, "FP64 SpMM needs 1 <= m <= 256 columns");
     if (C.n_rows == 0) return OTM_OK;
     m2_dispatch(m, reinterpret_cast<uintptr_t>(X) % 16 == 0, [&](auto v2, auto nu) {
-        hipLaunchKernelGGL((spmm64_kernel<v2.value, nu.value>), dim3(m2_blocks(C.n_rows)), dim3(kM2Threads), 0, s, C, X,
-                           m, scale, Y);
+        if (paced(C, m))
+            hipLaunchKernelGGL(spmm64_paced_kernel<v2.value>, dim3(m2_blocks(C.n_rows)), dim3(kM2Threads), 0, s, C, X, m,
+                               scale, Y);
+        else
+            hipLaunchKernelGGL((spmm64_kernel<v2.value, nu.value>), dim3(m2_blocks(C.n_rows)), dim3(kM2Threads), 0, s, C,
+                               X, m, scale, Y);
     });
     return check_launch("spmm64_kernel");
 }

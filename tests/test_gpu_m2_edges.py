@@ -172,3 +172,34 @@ def test_workspace_is_all_that_is_written(n, d, m, per):
     assert torch.equal(O, otm.m2_apply(A, AT, False, 0.7, S))
     assert otm.lib().otm_m2_apply(A.c(), AT.c(), 0, 0.7, S.data_ptr(), m, O.data_ptr(), info.data_ptr(),
                                   ws.data_ptr(), size - 1, otm._stream()) == -7
+
+
+@pytest.mark.parametrize("n2,m,per", [(9000, 140, 33), (9000, 139, 33), (9000, 138, 32), (9000, 140, 31), (25000, 100, 40),
+                                      (25000, 99, 40), (12000, 256, 70), (20000, 128, 35)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_pairs_apply_both_loops(n2, m, per, weighted):
+    """Pairs V on both sides of the rule between the two loops of the plain product (size
+    of V, its width, entries per row; rows of every length mod 4), with columns out of range,
+    against dense float64."""
+    g = np.random.default_rng(n2 + m)
+    n = 400
+    ln = np.full(n, per)
+    ln[:8] += np.arange(8) - 4                        # rows that end inside a group of four
+    ln[8] = 0
+    ln[9] += 4 + per
+    r = np.repeat(np.arange(n), ln)
+    c = g.integers(0, n2, len(r)).astype(np.int32)
+    bad = g.random(len(r)) < 0.05
+    v = g.integers(1, 4, len(r)).astype(np.float32) if weighted else None
+    rp = np.concatenate([[0], np.cumsum(ln)]).astype(np.int32)
+    ci = np.where(bad, n2 + 5, c).astype(np.int32)
+    t = lambda x: None if x is None else torch.from_numpy(x).to(dev())
+    G2 = otm.DeviceCSR(n, n2, t(rp), t(ci), t(v))
+    eye = np.arange(n, dtype=np.int32)
+    G1T = otm.DeviceCSR(n, n, t(np.arange(n + 1, dtype=np.int32)), t(eye), None)
+    V = g.standard_normal((n2, m))
+    ref = np.zeros((n, m))
+    w = (np.ones(len(r)) if v is None else v.astype(np.float64)) * ~bad
+    np.add.at(ref, r, w[:, None] * V[c])
+    out = otm.pairs_apply(G1T, G2, torch.from_numpy(V).to(dev()))
+    assert rel(out.cpu().numpy(), ref / n) < 1e-14    # sums of at most 150 terms
