@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kM2Threads) void spmm64_paced_kernel(otm_csr C, con
 // Where that loop is the faster one: X past 10 MB in rows of more than 128 doubles, past 20 MB
 // in rows of 100 and more, and rows of C long enough to keep a pace.  Two products in
 // turn, us, the other loop and this: 10000 x 10000, nnz = 1e6, m = 160 214, 182, m = 200
-// 294, 203 (m = 128 150, 163); 5000 x 5000, nnz = 5e5, m = 256 118, 103 (m = 200 87, 102);
+// 294, 203 (m = 128 150, 163); 5000 x 5000, nnz = 5e5, m = 256 118, 95 (m = 200 87, 102);
 // 20000 x 20000, nnz = 2e6, m = 128 426, 342 (m = 100 332, 342); 30000 x 30000, nnz = 3e6, m = 100
 // 583, 521; (50000 x 50000, nnz = 1e6, m = 200 465, 471).
 bool paced(const otm_csr& C, int m) {

@@ -31,10 +31,14 @@ int dispatch_views(const SgdArgs& a, int restarts, bool aliased, hipStream_t st)
 //    with four chunks of the batch (k = 20, 100 rows: 1.20, 1.29; 64 rows: 1.15, 1.07;
 //    k = 16: 1.14, 1.03; k = 32: 1.36, 1.30);
 //  * three views without compensation at 65 <= k <= 96 with batches past 112 rows,
-//    whose staging no wave is left for (k = 72, 128 rows: 4.43, 4.60; 100: 4.43, 4.16).
+//    whose staging no wave is left for (k = 72, 128 rows: 4.43, 4.60; 100: 4.43, 4.16);
+//  * one view with compensation at 113 <= k <= 126 with batches of 90 rows and more: eight
+//    columns and no free wave, and the means fold into either (k = 113 .. 126, 128 rows:
+//    5.84, 6.19; 100: 5.73, 5.95; 96: 5.65, 5.74; 90: 5.67, 5.73; 80: 5.66, 5.61).
 bool grid_is_faster(const SgdArgs& a, bool aliased) {
     if (a.k <= 14) return true;
     if (a.k >= 17 && a.k <= 30) return a.batch > 64;
+    if (a.k >= 113 && a.k <= 126) return aliased && a.compensated && a.batch >= 90;
     return a.k >= 65 && a.k <= 96 && !aliased && !a.compensated && a.batch > 112;
 }
 

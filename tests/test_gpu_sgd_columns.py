@@ -50,3 +50,13 @@ def test_short_run(k, three, dtype, batch, tail, compensated, steps):
     otm.sgd_run(p, n, *Y, to_dev(ybar), torch.from_numpy(perm)[None].contiguous().to(dev()), P)
     torch.cuda.synchronize()
     assert rel(phi_cols(P) - Phi0, ref - Phi0) < (3e-2 if dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("k,three,compensated,batch",
+                         [(k, True, False, b) for k in (65, 78, 79, 95, 96) for b in (112, 113, 128)]
+                         + [(k, False, True, b) for k in (112, 113, 120, 126, 127) for b in (89, 90, 128)])
+@pytest.mark.parametrize("steps", [1, 4])
+def test_rules_between_the_kernels(k, three, compensated, batch, steps):
+    """Both sides of the rules that send BF16 runs of more than 30 components to the grid
+    kernel, with a ragged last batch (and the k whose last tile holds only padding)."""
+    test_short_run(k, three, "bf16", batch, batch - 29, compensated, steps)
