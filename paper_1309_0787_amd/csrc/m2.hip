@@ -20,6 +20,7 @@
 //
 // Malformed CSR cannot make these kernels read out of bounds: row ranges are
 // clamped to [0, nnz] and entries with a column outside [0, n_cols) are skipped.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -604,15 +605,15 @@ bool panels_fit(int rows, int m) {
     return m >= 32 && (int64_t)rows * m >= 2000000 && (int64_t)rows * panel_count(m) * kPanel < (int64_t(1) << 32);
 }
 
+// What a wave does for a row and panel beside its gathers is done panel_count times as
+// often as by rows, so the rows have to be long: from an average of 20 entries on (whole
+// call, us, by rows and by panels: 60000 x 60000, m = 100, 2 entries a row 74, 286, 10 187, 308, 15
+// 262, 313, 20 337, 318, 30 469, 375; 30000 x 30000, m = 256, 10 222, 361, 20 388, 367).
+constexpr int kPanelEntries = 20;
+
 int64_t panel_blocks(int rows, int per, int m) {
     const int64_t total = (int64_t)((rows + per - 1) / per) * panel_count(m);
     return kXcds * ((total + kXcds - 1) / kXcds);
-}
-
-// Workgroups of the first pass, each with its part of v
-size_t m2_vparts(int n, int d, int m) {
-    if (panels_fit(n, m) && panels_fit(d, m)) return ((size_t)n + kPanelRows - 1) / kPanelRows;
-    return m2_blocks(n);
 }
 
 // Shares of m2_split_kernel at most: enough to fill the device (32 waves a CU).  Room for
@@ -776,14 +777,19 @@ extern "C" size_t otm_m2_apply_workspace(int32_t n, int32_t d, int32_t k_tilde) 
     if (n < 0 || d < 0 || k_tilde < 1) return 0;
     const size_t m = k_tilde;
     size_t b = 2 * ws_round(sizeof(double) * (size_t)n) + ws_round(sizeof(double) * m);   // w1, w2, v
-    if (panels_fit(n, k_tilde)) {                         // padded T1 and S, u, M1, v's parts
+    if (panels_fit(n, k_tilde)) {
+        // padded T1 and S, u, M1, v's parts of either first pass; by rows the same without padding
         const size_t pitch = (size_t)panel_count(k_tilde) * kPanel;
+        size_t parts = m2_blocks(n);
         b += ws_round(sizeof(double) * pitch * n) + 2 * ws_round(sizeof(double) * (size_t)d);
-        if (panels_fit(d, k_tilde)) b += ws_round(sizeof(double) * pitch * d);
-        return b + ws_round(sizeof(double) * m2_vparts(n, d, k_tilde) * pitch);
+        if (panels_fit(d, k_tilde)) {
+            b += ws_round(sizeof(double) * pitch * d);
+            parts = std::max(parts, ((size_t)n + kPanelRows - 1) / kPanelRows);
+        }
+        return b + ws_round(sizeof(double) * parts * pitch);
     }
     b += ws_round(sizeof(double) * (size_t)n * m);        // T1, v's parts, the shares' sums
-    b += ws_round(sizeof(double) * m2_vparts(n, d, k_tilde) * m);
+    b += ws_round(sizeof(double) * (size_t)m2_blocks(n) * m);
     return b + ws_round(sizeof(double) * (size_t)2 * m2_shares(d) * (m + 2));
 }
 
@@ -804,9 +810,19 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
                 "m2_apply workspace too small");
     hipStream_t s = as_stream(stream);
     WsCarver wc(ws, ws_bytes);
-    if (panels_fit(n, k_tilde)) {
+    // Rows of C^T of 256 entries and more (documents: a word occurs in thousands
+    // of them) are too few to fill the device evenly, and their lengths differ by
+    // orders of magnitude: there the entries are split instead of the rows, or by panels a
+    // workgroup takes each row and panel, where a launch holds as many.  Panels of 64 rows a
+    // workgroup need enough of those (100000 x 5000, 5 entries a row of C: m = 64, 395
+    // workgroups, 98 us by rows, 134; m = 200, 1106, 237, 234).
+    const bool rows_long = CT->nnz >= (int64_t)256 * d;
+    const bool one_row = rows_long && panel_blocks(d, 1, k_tilde) * kM2Threads < (int64_t(1) << 32);
+    const bool panels = panels_fit(n, k_tilde) && CT->nnz >= (int64_t)kPanelEntries * d &&
+                        (one_row || panel_blocks(d, kPanelRows, k_tilde) >= 1024);
+    if (panels) {
         const int pitch = panel_count(k_tilde) * kPanel;
-        const bool both = panels_fit(d, k_tilde);
+        const bool both = panels_fit(d, k_tilde) && C->nnz >= (int64_t)kPanelEntries * n;
         double* T1 = wc.take<double>((size_t)pitch * n);
         double* Sp = wc.take<double>(both ? (size_t)pitch * d : 0);
         double* w1 = wc.take<double>(n);
@@ -814,7 +830,7 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
         double* u = wc.take<double>(d);
         double* M1 = wc.take<double>(d);
         double* v = wc.take<double>(k_tilde);
-        const int nb = static_cast<int>(m2_vparts(n, d, k_tilde));
+        const int nb = both ? (n + kPanelRows - 1) / kPanelRows : m2_blocks(n);
         double* vpart = wc.take<double>((size_t)pitch * nb);
         hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, s, info, 0);
         if ((st = check_launch("set_i32_kernel")) != OTM_OK) return st;
@@ -843,10 +859,8 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
                                    dim3((unsigned)panel_blocks(d, LONG ? 1 : kPanelRows, k_tilde)), dim3(kM2Threads), 0, s, *CT, T1,
                                    k_tilde, E, ldS, u, M1);
             };
-            // (a workgroup to each row and panel, where a launch holds as many)
-            const bool rows_long = CT->nnz >= (int64_t)256 * d && panel_blocks(d, 1, k_tilde) * kM2Threads < (int64_t(1) << 32);
-            if (!normalize) rows_long ? second(std::true_type{}, std::true_type{}) : second(std::false_type{}, std::true_type{});
-            else rows_long ? second(std::true_type{}, std::false_type{}) : second(std::false_type{}, std::false_type{});
+            if (!normalize) one_row ? second(std::true_type{}, std::true_type{}) : second(std::false_type{}, std::true_type{});
+            else one_row ? second(std::true_type{}, std::false_type{}) : second(std::false_type{}, std::false_type{});
             if ((st = check_launch("m2_panel2_kernel")) != OTM_OK) return st;
             if (normalize) {
                 hipLaunchKernelGGL(m2_epilogue_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, O, S, u, M1,
@@ -859,17 +873,14 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
     double* T1 = wc.take<double>((size_t)n * k_tilde);
     double* w1 = wc.take<double>(n);
     double* w2 = wc.take<double>(n);
-    const int b1 = static_cast<int>(m2_vparts(n, d, k_tilde));
+    const int b1 = m2_blocks(n);
     double* vpart = wc.take<double>((size_t)b1 * k_tilde);
     double* v = wc.take<double>(k_tilde);
-    double* part = wc.take<double>((size_t)2 * m2_shares(d) * (k_tilde + 2));
+    double* part = wc.take<double>(panels_fit(n, k_tilde) ? 0 : (size_t)2 * m2_shares(d) * (k_tilde + 2));
     hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, s, info, 0);
     if ((st = check_launch("set_i32_kernel")) != OTM_OK) return st;
     const M2End E{S, v, O, 1.0 / n, (alpha0 + 1.0) / n, alpha0};
-    // Rows of C^T of 256 entries and more (documents: a word occurs in thousands
-    // of them) are too few to fill the device evenly, and their lengths differ by
-    // orders of magnitude: there the entries are split instead of the rows.
-    const bool split = d >= 1 && CT->nnz >= (int64_t)256 * d;
+    const bool split = d >= 1 && rows_long && !panels_fit(n, k_tilde);   // (the others have no room for the parts, nor need it)
     int64_t L = split ? (CT->nnz + m2_shares(d) - 1) / m2_shares(d) : 1;
     L = L < 256 ? 256 : (L + 63) / 64 * 64;
     const uintptr_t at = reinterpret_cast<uintptr_t>(S) | reinterpret_cast<uintptr_t>(T1) |

@@ -148,7 +148,8 @@ def test_many_long_rows():
 
 
 @pytest.mark.parametrize("n,d,m,per", [(300, 200, 40, 5), (20000, 70, 20, 40), (3000, 9, 256, 6), (42000, 41000, 50, 4),
-                                       (64000, 90, 32, 6), (42000, 41000, 49, 5)])
+                                       (64000, 90, 32, 6), (42000, 41000, 49, 5),
+                                       (42000, 41000, 50, 24), (42000, 41000, 49, 25), (110000, 5000, 60, 6)])
 def test_workspace_is_all_that_is_written(n, d, m, per):
     """The layout of every path stays inside the size that the workspace function gives: bytes past
     it keep their value, and the result is that of a roomier one."""
@@ -203,3 +204,13 @@ def test_pairs_apply_both_loops(n2, m, per, weighted):
     np.add.at(ref, r, w[:, None] * V[c])
     out = otm.pairs_apply(G1T, G2, torch.from_numpy(V).to(dev()))
     assert rel(out.cpu().numpy(), ref / n) < 1e-14    # sums of at most 150 terms
+
+
+@pytest.mark.parametrize("n,d,m,per_row,normalize",
+                         [(41000, 40500, 50, 24, False), (41000, 40500, 51, 24, True), (42000, 40000, 62, 21, True),
+                          (42000, 40000, 62, 20, False), (42000, 40000, 62, 19, True), (30000, 60000, 80, 45, False),
+                          (60000, 30000, 80, 15, True), (63000, 12000, 100, 5, False), (63000, 12000, 100, 3, True)])
+def test_m2_apply_row_lengths(n, d, m, per_row, normalize):
+    """Both sides of the rules that take rows by panels: 20 entries a row of C^T for the
+    second pass and of C for the first, and workgroups enough."""
+    test_m2_apply_panels(n, d, m, per_row, normalize)
