@@ -815,7 +815,7 @@ extern "C" int otm_m2_apply(const otm_csr* C, const otm_csr* CT, int normalize, 
     // orders of magnitude: there the entries are split instead of the rows, or by panels a
     // workgroup takes each row and panel, where a launch holds as many.  Panels of 64 rows a
     // workgroup need enough of those (100000 x 5000, 5 entries a row of C: m = 64, 395
-    // workgroups, 98 us by rows, 134; m = 200, 1106, 237, 234).
+    // workgroups, 98 us by rows, 134; m = 200, 1027, 237, 234).
     const bool rows_long = CT->nnz >= (int64_t)256 * d;
     const bool one_row = rows_long && panel_blocks(d, 1, k_tilde) * kM2Threads < (int64_t(1) << 32);
     const bool panels = panels_fit(n, k_tilde) && CT->nnz >= (int64_t)kPanelEntries * d &&

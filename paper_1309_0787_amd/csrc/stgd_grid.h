@@ -81,10 +81,6 @@ struct MmaF32 {
     __device__ static Op to_op(float x) { return x; }
     __device__ static float op_to_f(Op x) { return x; }
     __device__ static Frag zero_frag() { return 0.0f; }
-    // fragment of EPL consecutive row elements a0.. (masked at k)
-    __device__ static Frag yrow(const Y* row, int a0, int k) {
-        return (row != nullptr && a0 < k) ? row[a0] : 0.0f;
-    }
     // elements e >= valid of a row piece set to 0 (the padding past k)
     __device__ static Chunk mask_chunk(Chunk v, int valid) {
 #pragma unroll
@@ -131,8 +127,7 @@ struct MmaBF16 {
     // pitch the 8-byte stores of a product's output tile (lane l: row l % 16,
     // piece l / 16) hit each bank twice as often as they need to (16 cycles
     // per wave); with the permutation they take 8 (a contiguous 8-byte store
-    // takes 6.6), while the fragment reads stay conflict-free (measured on
-    // gfx950; BF16 k = 100 step 5.02 -> 4.85 us).
+    // takes 6.6), while the fragment reads stay conflict-free (measured on gfx950).
     __device__ static constexpr int sw(int r) { return ((r >> 2) & 1) << 3; }
     // Fragment of a matrix stored the other way round: lane l receives
     // X[8 (l/16) + e][l % 16], e < 8, where X[r][c] = x[r * stride + c] in
@@ -171,17 +166,6 @@ struct MmaBF16 {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16(0.0f);
         return v;
-    }
-    __device__ static Frag yrow(const Y* row, int a0, int k) {
-        if (row != nullptr && a0 < k) {
-            // ldy % 8 == 0 and a0 % 8 == 0: the 16-byte load stays inside the row
-            bf16x8 v = *reinterpret_cast<const bf16x8*>(row + a0);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (a0 + e >= k) v[e] = f32_to_bf16(0.0f);
-            return v;
-        }
-        return zero_frag();
     }
     __device__ static Chunk mask_chunk(Chunk v, int valid) {
 #pragma unroll
@@ -225,7 +209,6 @@ __device__ __forceinline__ f32x4 yrow4(const float* row, int a0, int k) {
         if (a0 + e < k) v[e] = row[a0 + e];
     return v;
 }
-__device__ __forceinline__ f32x4 yrow4(const __bf16*, int, int) { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
 template <class M, int KP, int NSTAGE, int WR = 4>
 struct SgdSmem {
@@ -312,10 +295,9 @@ __device__ __forceinline__ void sgd_body_t(const SgdArgs& g, const int r_id, Sgd
     constexpr int KQ = KP / 4;                     // FP32: k range of one lane group
     constexpr int NCH = (MB * cpr + kThreads - 1) / kThreads;   // chunks per thread when staging
     constexpr int UNR = (M::KI >= 32) ? 4 : 2;     // unroll of the k x k and D contraction loops
-    // and of the batch products: fully unrolled for staged BF16 rows (the first
-    // MFMA then starts from zero without clearing registers); FP32 and
-    // unstaged rows spill registers beyond 2
-    constexpr int UNR_P = (M::EPL == 8 && NSTAGE > 0) ? 4 : 2;
+    // and of the batch products: fully unrolled in BF16 (the first MFMA then starts
+    // from zero without clearing registers); FP32 spills registers beyond 2
+    constexpr int UNR_P = M::EPL == 8 ? 4 : 2;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1026,13 +1008,8 @@ __device__ __forceinline__ void sgd_body_t(const SgdArgs& g, const int r_id, Sgd
 #pragma unroll UNR_P
                 for (int k0 = 0; k0 < KP; k0 += M::KI) {
                     typename M::Frag fa, fbv;
-                    if constexpr (NSTAGE == 0) {
-                        fa = M::yrow(rowA, k0 + q * M::EPL, k);
-                        fbv = M::yrow(rowB, k0 + q * M::EPL, k);
-                    } else {
-                        fa = M::lds(sA + k0 + q * M::EPL);
-                        if constexpr (NSTAGE == 3) fbv = M::lds(sB + k0 + q * M::EPL);
-                    }
+                    fa = M::lds(sA + k0 + q * M::EPL);
+                    if constexpr (NSTAGE == 3) fbv = M::lds(sB + k0 + q * M::EPL);
 #pragma unroll
                     for (int tj = 0; tj < TC; ++tj) {
                         const int nt = wc + WC * tj;
@@ -1108,13 +1085,7 @@ if constexpr (M::EPL == 1 && NSTAGE > 0) {
                         for (int ti = 0; ti < TRK; ++ti) {
                             const int mt = wr + WR * ti;
                             const int a = mt * 16 + l16;
-                            if (ti >= TRL) {
-                                fa1[ti] = 0.0f;
-                            } else if constexpr (NSTAGE > 0) {
-                                fa1[ti] = sm.ybatch[(vc * MB + tr) * SY + a];
-                            } else {
-                                fa1[ti] = (a < k && tr < nb) ? Yv[2][(size_t)sm.idx[tr] * ldy + a] : 0.0f;
-                            }
+                            fa1[ti] = ti < TRL ? sm.ybatch[(vc * MB + tr) * SY + a] : 0.0f;
                         }
 #pragma unroll
                         for (int ti = 0; ti < TRK; ++ti)
@@ -1135,11 +1106,7 @@ if constexpr (M::EPL == 1 && NSTAGE > 0) {
                         fa[ti] = M::zero_frag();
                     } else if constexpr (NSTAGE > 0) {
                         // EPL rows t = k0 + EPL*q + e of column a of the staged batch
-                        if constexpr (M::EPL == 1) {
-                            fa[ti] = sm.ybatch[(vc * MB + k0 + q) * SY + a];
-                        } else {
-                            fa[ti] = M::lds_t(&sm.ybatch[(vc * MB + k0) * SY + mt * 16], SY, lane);
-                        }
+                        fa[ti] = M::lds_t(&sm.ybatch[(vc * MB + k0) * SY + mt * 16], SY, lane);
                     } else {
                         const int tr = k0 + q;
                         fa[ti] = (a < k && tr < nb) ? Yv[2][(size_t)sm.idx[tr] * ldy + a] : 0.0f;

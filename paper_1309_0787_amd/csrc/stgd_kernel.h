@@ -72,7 +72,6 @@ struct Mma {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
     __device__ static Op to_op(float x) { return f32_to_bf16(x); }
-    __device__ static float op_to_f(Op x) { return bf16_to_f32(x); }
     // sw: the row's column permutation (Phi copy), 0 for the batch
     __device__ static Frag row(const Op* x, int q, int sw) {
         return *reinterpret_cast<const bf16x8*>(x + ((8 * q) ^ sw));
@@ -150,7 +149,6 @@ struct Mma {
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
     }
     __device__ static float elem(Frag f, int e) { return bf16_to_f32(f[e]); }
-    __device__ static Chunk zero_chunk() { return __builtin_bit_cast(Chunk, u32x4{0u, 0u, 0u, 0u}); }
     __device__ static u32x4 chunk_mask(int valid) {
         u32x4 m;
 #pragma unroll
@@ -242,7 +240,6 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
     const int32_t* perms = g.perms ? g.perms + (size_t)r_id * g.perm_stride : nullptr;
     const Y* Yv[3] = {static_cast<const Y*>(g.YA), static_cast<const Y*>(g.YB), static_cast<const Y*>(g.YC)};
     bool bad = false;
-    const float cmask = g.compensated ? 1.0f : 0.0f;
     // mA = Phi^T ybarA and mB = Phi^T ybarB ride along in Phi^T Phi when a wave
     // has all rows of its column and two padding rows are free: rows k, k + 1 of
     // the Phi copy hold ybarA, ybarB, so G[k][i] = mA[i], G[k + 1][i] = mB[i]
@@ -261,7 +258,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
             const int a = mt * 16 + 4 * q + r;
             if (lane_live && a < k) {
                 v[r] = Phi0[(size_t)i * k + a];
-                if (Comp && g.compensated) cv[r] = Comp[(size_t)i * k + a];
+                if (COMP && Comp) cv[r] = Comp[(size_t)i * k + a];
             }
         }
         phi_r[mt] = v;
@@ -766,10 +763,10 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
                     f32x4 cv = comp[mt];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        // Kahan step; cmask = 0 turns it into the plain update
+                        // Kahan step
                         const float u = fmaf(f1, d[r], fmaf(f2, ybc[r], -cv[r]));
                         const float s = v[r] + u;
-                        cv[r] = ((s - v[r]) - u) * cmask;
+                        cv[r] = (s - v[r]) - u;
                         v[r] = s;
                     }
                     comp[mt] = cv;
@@ -826,7 +823,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& g, const int r_id, typen
             if (lane_live && a < k) {
                 Phi[(size_t)i * k + a] = phi_r[mt][r];
                 if (Comp) {
-                    if constexpr (COMP) Comp[(size_t)i * k + a] = g.compensated ? comp[mt][r] : 0.0f;
+                    if constexpr (COMP) Comp[(size_t)i * k + a] = comp[mt][r];
                     else Comp[(size_t)i * k + a] = 0.0f;
                 }
             }
