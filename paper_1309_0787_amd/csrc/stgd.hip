@@ -24,22 +24,28 @@ int dispatch_views(const SgdArgs& a, int restarts, bool aliased, hipStream_t st)
     return aliased ? launch_sgd<NT, true>(a, restarts, st) : launch_sgd<NT, false>(a, restarts, st);
 }
 
-// BF16 runs that the grid kernel steps through faster, us a step (grid, columns):
-//  * k <= 14, the components and the two folded means in one tile: one chain of
-//    latencies whatever the split (k = 10: 0.89, 1.07);
+// BF16 runs that the grid kernel steps through faster, us a step (grid, columns), measured
+// at every k and eleven batch sizes up to 32 components, at 14 k and nine sizes around
+// the others:
+//  * k <= 14, the components and the two folded means in one tile, with batches past 48 rows
+//    (one view with compensation: 64): one chain of latencies whatever the split, which a column
+//    walks once per chunk (k = 10, one view: 16 rows 0.86, 0.74, 48 0.87, 0.88, 64 0.88,
+//    0.94, 128 0.86, 1.06; compensated 64 0.99, 0.97, 65 0.99, 1.08);
 //  * 17 <= k <= 30 with batches past 64 rows: two tile columns leave a wave each
-//    with four chunks of the batch (k = 20, 100 rows: 1.20, 1.29; 64 rows: 1.15, 1.07;
+//    with four chunks of the batch (128 rows: k = 17 1.13, 1.24, k = 30 1.13, 1.25, three views k =
+//    24 1.35, 1.43; even with compensation: k = 24 1.26, 1.23; 64 rows: k = 20 1.01, 1.01;
 //    k = 16: 1.14, 1.03; k = 32: 1.36, 1.30);
-//  * three views without compensation at 65 <= k <= 96 with batches past 112 rows,
-//    whose staging no wave is left for (k = 72, 128 rows: 4.43, 4.60; 100: 4.43, 4.16);
+//  * three views without compensation at 65 <= k <= 78 with batches past 112 rows,
+//    whose staging no wave is left for (128 rows: k = 65 4.25, 4.31, k = 78 4.26, 4.33, but k = 79, a
+//    tile more in the grid, 4.71, 4.52; 112: k = 72 3.99, 4.00);
 //  * one view with compensation at 113 <= k <= 126 with batches of 90 rows and more: eight
 //    columns and no free wave, and the means fold into either (k = 113 .. 126, 128 rows:
 //    5.84, 6.19; 100: 5.73, 5.95; 96: 5.65, 5.74; 90: 5.67, 5.73; 80: 5.66, 5.61).
 bool grid_is_faster(const SgdArgs& a, bool aliased) {
-    if (a.k <= 14) return true;
+    if (a.k <= 14) return a.batch > (aliased && a.compensated ? 64 : 48);
     if (a.k >= 17 && a.k <= 30) return a.batch > 64;
     if (a.k >= 113 && a.k <= 126) return aliased && a.compensated && a.batch >= 90;
-    return a.k >= 65 && a.k <= 96 && !aliased && !a.compensated && a.batch > 112;
+    return a.k >= 65 && a.k <= 78 && !aliased && !a.compensated && a.batch > 112;
 }
 
 // BF16: the instantiation with the fewest tile columns that hold k components.

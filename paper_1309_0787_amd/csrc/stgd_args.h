@@ -29,7 +29,7 @@ struct SgdArgs {
 };
 
 // The grid kernel's single runs (stgd_grid.hip): FP32, and the BF16 ones of
-// grid_is_faster (stgd.hip): k <= 30; 65 <= k <= 96, three views without compensation;
+// grid_is_faster (stgd.hip): k <= 30; 65 <= k <= 78, three views without compensation;
 // 113 <= k <= 126, one view with it.
 int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);

@@ -54,7 +54,7 @@ int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_
 // hold only padding and are skipped
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
     if (a.k > 96) return launch<MmaBF16, 128, 1, true, 8, false>(a, restarts, st);
-    if (a.k > 32) return a.k + 2 <= 80 ? launch<MmaBF16, 96, 3, false, 5, false>(a, restarts, st) : launch<MmaBF16, 96, 3, false, 6, false>(a, restarts, st);
+    if (a.k > 32) return launch<MmaBF16, 96, 3, false, 5, false>(a, restarts, st);
     if (a.k + 2 <= 16) return bf16_small<1>(a, restarts, aliased, st);
     return bf16_small<2>(a, restarts, aliased, st);
 }

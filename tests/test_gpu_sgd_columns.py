@@ -54,9 +54,11 @@ def test_short_run(k, three, dtype, batch, tail, compensated, steps):
 
 @pytest.mark.parametrize("k,three,compensated,batch",
                          [(k, True, False, b) for k in (65, 78, 79, 95, 96) for b in (112, 113, 128)]
-                         + [(k, False, True, b) for k in (112, 113, 120, 126, 127) for b in (89, 90, 128)])
+                         + [(k, False, True, b) for k in (112, 113, 120, 126, 127) for b in (89, 90, 128)]
+                         + [(k, three, c, b) for k in (1, 10, 14, 16, 17, 30) for three in (False, True)
+                            for c, b in ((False, 48), (False, 49), (True, 64), (True, 65))])
 @pytest.mark.parametrize("steps", [1, 4])
 def test_rules_between_the_kernels(k, three, compensated, batch, steps):
-    """Both sides of the rules that send BF16 runs of more than 30 components to the grid
+    """Both sides of the rules that send BF16 runs to the grid
     kernel, with a ragged last batch (and the k whose last tile holds only padding)."""
     test_short_run(k, three, "bf16", batch, batch - 29, compensated, steps)
