@@ -18,7 +18,7 @@
 // What bounds it: the reduction is n - 2 dependent steps on one CU (matrix in
 // registers, two barriers a step); everything else is spread over the device but
 // short, so launches and latencies count.  The eigenproblems of a whitener with 200
-// and 100 columns: 8740 us by rotations -> 1170 (the reduction 2 x 363 of it).
+// and 100 columns: 8740 us by rotations -> 1280 (the reduction 2 x 367 of it).
 #include <cfloat>
 #include <cmath>
 

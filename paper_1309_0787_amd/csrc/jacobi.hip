@@ -376,9 +376,11 @@ int jacobi(double* A, double* V, int n, double* evals, int* order, void* ws, hip
         int* lp = wc.take<int>(log_entries(n));
         int* rounds = wc.take<int>(1);
         int* redo = nullptr;
-        // From 33 on the direct solver is the faster one (a whitener with kt = 40, k = 20,
-        // all of it: 471 us by rotations, 266 with the larger problem direct; kt = 48, k =
-        // 24 656, 297; kt = 32 367, even).  A matrix that is nearly diagonal takes few
+        // From 33 on the direct solver runs (a whitener with kt = 40, k = 20, all of it: 552
+        // us by rotations, 252 with the larger problem direct; kt = 64, k = 32 863, 348; kt = 200, k
+        // = 100, both 7061, 1140).  It would be the faster one below too (k = 6: kt = 16 163,
+        // 157, kt = 20 195, 172, kt = 24 248, 182, kt = 32 318, 207); the line is where the first form
+        // of it, with both problems of a whitener direct, was even.  A matrix that is nearly diagonal takes few
         // sweeps: there it pays from 65 on (kt = 80, k = 40 444 with the Gram of 40 by
         // rotations, 572 direct), and for one that is diagonal as a rule never (the Gram of a
         // whitener's columns in the unwhitening, one sweep: k = 33, d = 500, all of the call

@@ -14,7 +14,8 @@
 // an entry costs the vector memory unit one or two wide loads and nothing else
 // (with the index, the value and both weights loaded for every entry, each as a
 // broadcast, it was five to six: documents' first pass 2044 -> 883 us, 17 TB/s of
-// gathers, S stays in L2).  Matrices past 16 MB are taken by panels of 16 columns.
+// gathers from an S of 8 MB, two XCD L2s).  Matrices past 16 MB whose rows are long enough
+// are taken by panels of 16 columns.
 // Whole calls before all of this and now, us: documents (d = 10000, nnz = 1.9e7, m =
 // 100) 6600 -> 2540, graph (n = d = 50000, nnz = 3.7e6, m = 200) 1800 -> 1016.
 //

@@ -33,7 +33,7 @@
 // with two or three LDS trips that nothing covers.  The kernel that split every
 // product over a grid of waves and took G*G and Q through LDS (four barriers a
 // step) measured, before and after, us per step: k = 100 one view 4.2 -> 3.6
-// (compensated 4.9 -> 3.9), three views 16.2 -> 5.0 (compensated 16.5 -> 6.3;
+// (compensated 4.9 -> 3.9), three views 16.2 -> 5.0 (compensated 16.5 -> 5.9;
 // there the views did not fit beside the exchange buffer and were read from
 // global memory inside the products), k = 128 5.8 -> 4.8, k = 80 3.6 -> 2.9,
 // k = 64 2.3 -> 1.8, k = 48 2.0 -> 1.6, k = 32 1.3 -> 1.2.  Two columns per wave

@@ -72,9 +72,9 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __
 // partials over node split z: cross[z][i][j] = sum_x (a_ix - abar_i)(b_jx - bbar_j),
 // l1[z][i][j] = sum_x |a_ix - b_jx|.  A thread owns 4 x 4 pairs, so a node costs it
 // four 16-byte LDS reads and 56 FP64 operations (16 x 16 pairs per workgroup, one
-// per thread, took two reads for 4: k_hat = k = 100, n = 50000 282 -> 169 us; the
-// additions and products alone take 60 at full rate; on the matrix cores the cross
-// sums made it 224).
+// per thread, took two reads for 4: k_hat = k = 100, n = 50000 282 -> 126 us; the
+// additions and products alone take 60 at full rate; with ranges of 384 nodes it took 169,
+// and the cross sums on the matrix cores made that 224).
 __global__ __launch_bounds__(256) void pair_stats_kernel(const float* __restrict__ Ph, int kh,
                                                          const float* __restrict__ P, int k, int n, int per,
                                                          const double* __restrict__ mean, double* __restrict__ cross,
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * kFinParts) void finalize_kernel(const double* 
 
 // rank[e] += values among p[f0 .. f0 + kRankSpan) that come before p[e] (ties: lower
 // position first); whole numbers, so the order of the additions does not matter.
-// One workgroup per span and 256 values: 10000 values 297 -> 25 us (one thread
+// One workgroup per span and 256 values: 10000 values 297 -> 14 us (one thread
 // went over all of them for each value).
 constexpr int kRankThreads = 256;
 constexpr int kRankSpan = 256;

@@ -7,7 +7,7 @@ one or on properties that hold at any size.
   sign rule); whitening of 2000 sampled rows against the oracle's rows from
   the same BF16 W (one BF16 rounding of the FP32 accumulators: 8e-3 per row);
   the means 1e-6; one STGD step of the benchmark's kernel
-  (sgd_kernel<BF16, 128, staged>) from a pass-end snapshot against the oracle
+  (sgd_kernel<7, one view>) from a pass-end snapshot against the oracle
   step on the same BF16 rows (the BF16 step bar 3e-2); the full 50-pass BF16
   run (25,000 steps) against the FP64 oracle run from the same initial
   factors and permutations: relative factor error at most 1e-2 (the BF16 run
