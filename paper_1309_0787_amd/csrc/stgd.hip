@@ -40,8 +40,21 @@ int dispatch_views(const SgdArgs& a, int restarts, bool aliased, hipStream_t st)
 //    tile more in the grid, 4.71, 4.52; 112: k = 72 3.99, 4.00);
 //  * one view with compensation at 113 <= k <= 126 with batches of 90 rows and more: eight
 //    columns and no free wave, and the means fold into either (k = 113 .. 126, 128 rows:
-//    5.84, 6.19; 100: 5.73, 5.95; 96: 5.65, 5.74; 90: 5.67, 5.73; 80: 5.66, 5.61).
-bool grid_is_faster(const SgdArgs& a, bool aliased) {
+//    5.84, 6.19; 100: 5.73, 5.95; 96: 5.65, 5.74; 90: 5.67, 5.73; 80: 5.66, 5.61);
+//  * more restarts than the 256 CUs: up to 128 registers a lane, as in the grid kernel at KP <= 64,
+//    two workgroups share a CU, and the columns with one view past k = 16 or three views hold
+//    more (140 to 256).  Three views at k <= 32 and one view at 17 <= k <= 64 then gain, but with
+//    batches up to 48 rows not k = 47, 48, 63, 64, whose two folded means take the grid kernel a
+//    tile more or a pass of their own (512 restarts, 10 steps, us for the run: three
+//    views, 100 rows, k = 16 22.4, 33.0, k = 32 25.1, 36.4; one view, 64 rows, k = 20 19.2,
+//    27.1, 100 rows, k = 32 22.0, 31.5, k = 40 30.2, 40.1, k = 56 40.0, 47.0, k = 64 44.3, 49.1,
+//    but 32 rows, k = 64 43.1, 40.6, and k = 16, 100 rows, 19.1, 15.0).
+constexpr int kCus = 256;
+bool grid_is_faster(const SgdArgs& a, bool aliased, int restarts) {
+    if (restarts > kCus) {
+        if (!aliased && a.k <= 32) return true;
+        if (aliased && a.k >= 17 && a.k <= 64) return a.k <= 46 || (a.k >= 49 && a.k <= 62) || a.batch > 48;
+    }
     if (a.k <= 14) return a.batch > (aliased && a.compensated ? 64 : 48);
     if (a.k >= 17 && a.k <= 30) return a.batch > 64;
     if (a.k >= 113 && a.k <= 126) return aliased && a.compensated && a.batch >= 90;
@@ -50,7 +63,7 @@ bool grid_is_faster(const SgdArgs& a, bool aliased) {
 
 // BF16: the instantiation with the fewest tile columns that hold k components.
 int dispatch_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    if (grid_is_faster(a, aliased)) return launch_sgd_grid_bf16(a, restarts, aliased, st);
+    if (grid_is_faster(a, aliased, restarts)) return launch_sgd_grid_bf16(a, restarts, aliased, st);
     switch ((a.k + 15) / 16) {
         case 1: return dispatch_views<1>(a, restarts, aliased, st);
         case 2: return dispatch_views<2>(a, restarts, aliased, st);

@@ -28,9 +28,9 @@ struct SgdArgs {
     float beta0, inv_tau;
 };
 
-// The grid kernel's single runs (stgd_grid.hip): FP32, and the BF16 ones of
-// grid_is_faster (stgd.hip): k <= 30; 65 <= k <= 78, three views without compensation;
-// 113 <= k <= 126, one view with it.
+// The grid kernel's runs (stgd_grid.hip): FP32, and the BF16 ones of grid_is_faster
+// (stgd.hip): k <= 32; 33 <= k <= 64, one view; 65 <= k <= 78, three views without
+// compensation; 113 <= k <= 126, one view with it.
 int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st);
 

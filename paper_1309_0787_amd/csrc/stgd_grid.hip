@@ -27,11 +27,15 @@ int f32_run(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
                    : launch<MmaF32, KP, s3, true, KP / 16, false>(a, restarts, st);
 }
 
+template <int KP, int NSTAGE, int NTL>
+int bf16_run(const SgdArgs& a, int restarts, hipStream_t st) {
+    return a.compensated ? launch<MmaBF16, KP, NSTAGE, true, NTL, false>(a, restarts, st)
+                         : launch<MmaBF16, KP, NSTAGE, false, NTL, false>(a, restarts, st);
+}
+
 template <int NTL>
 int bf16_small(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
-    if (a.compensated)
-        return aliased ? launch<MmaBF16, 32, 1, true, NTL, false>(a, restarts, st) : launch<MmaBF16, 32, 3, true, NTL, false>(a, restarts, st);
-    return aliased ? launch<MmaBF16, 32, 1, false, NTL, false>(a, restarts, st) : launch<MmaBF16, 32, 3, false, NTL, false>(a, restarts, st);
+    return aliased ? bf16_run<32, 1, NTL>(a, restarts, st) : bf16_run<32, 3, NTL>(a, restarts, st);
 }
 
 }  // namespace
@@ -54,7 +58,8 @@ int launch_sgd_grid_f32(const SgdArgs& a, int restarts, bool aliased, hipStream_
 // hold only padding and are skipped
 int launch_sgd_grid_bf16(const SgdArgs& a, int restarts, bool aliased, hipStream_t st) {
     if (a.k > 96) return launch<MmaBF16, 128, 1, true, 8, false>(a, restarts, st);
-    if (a.k > 32) return launch<MmaBF16, 96, 3, false, 5, false>(a, restarts, st);
+    if (a.k > 64) return launch<MmaBF16, 96, 3, false, 5, false>(a, restarts, st);
+    if (a.k > 32) return a.k + 2 <= 48 ? bf16_run<64, 1, 3>(a, restarts, st) : bf16_run<64, 1, 4>(a, restarts, st);
     if (a.k + 2 <= 16) return bf16_small<1>(a, restarts, aliased, st);
     return bf16_small<2>(a, restarts, aliased, st);
 }

@@ -62,3 +62,32 @@ def test_rules_between_the_kernels(k, three, compensated, batch, steps):
     """Both sides of the rules that send BF16 runs to the grid
     kernel, with a ragged last batch (and the k whose last tile holds only padding)."""
     test_short_run(k, three, "bf16", batch, batch - 29, compensated, steps)
+
+
+@pytest.mark.parametrize("k,three,batch", [(16, False, 32), (17, False, 33), (31, False, 100), (46, False, 17), (47, False, 48),
+                                           (47, False, 49), (49, False, 16), (62, False, 100), (63, False, 49), (64, False, 128), (65, False, 48),
+                                           (3, True, 17), (14, True, 48), (16, True, 100), (32, True, 33), (33, True, 48)])
+@pytest.mark.parametrize("compensated", [False, True])
+@pytest.mark.parametrize("restarts", [256, 257])
+def test_more_restarts_than_cus(k, three, batch, compensated, restarts):
+    """Both sides of the rule for many restarts: two workgroups to a CU.  Every restart
+    has the same start and rows, so all end with the same bits; they match the oracle."""
+    steps, tail = 3, batch // 2 + 1
+    n = (steps - 1) * batch + tail
+    g = np.random.default_rng(1000 * k + batch)
+    views = [bf16_round(g.standard_normal((n, k)) * 0.3 + s) for s in ((0.2, 0.1, -0.1) if three else (0.2,))]
+    views = views if three else views * 3
+    ybar = f32_round(np.stack([v.mean(0) for v in views]))
+    Phi0 = f32_round(synth.initial_factors(k, seed=k) * 1.1)
+    ref = Phi0
+    for t in range(steps):
+        rows = slice(t * batch, (t + 1) * batch)
+        ref = oracle.sgd_step(views[0][rows], views[1][rows], views[2][rows], ybar, ref, 0.01 / (1 + t / 50.0), 0.5)
+    Y = [padded(v, otm.default_ldy(k), torch.bfloat16) for v in (views if three else views[:1])]
+    P = phi_rows(Phi0).repeat(restarts, 1, 1).contiguous()
+    p = otm.SgdParams(k=k, batch=batch, passes=1, alpha0=0.5, beta0=0.01, beta_tau=50.0, compensated=compensated,
+                      y_dtype=otm.BF16)
+    otm.sgd_run(p, n, *(Y if three else Y * 3), to_dev(ybar), None, P, restarts=restarts)
+    torch.cuda.synchronize()
+    assert torch.equal(P, P[:1].expand_as(P))
+    assert rel(phi_cols(P[0]) - Phi0, ref - Phi0) < 3e-2
